@@ -133,30 +133,25 @@ hipError_t launch_ras_tile(const Geom& g, int tile, int si, int sj, int inner, b
 
 // ----------------------------------------------------------------- krylov.hip
 int flat_blocks(size_t n);
-// partial[i * nblk + b] = sum over block b of V_i . w (any nv, in chunks of 8); when
-// norm_slot >= 0 also partial[norm_slot * nblk + b] = block sums of w . w
+// partial[i * nblk + b] = sum over block b of V_i . w (any nv); when norm_slot >= 0
+// also partial[norm_slot * nblk + b] = block sums of w . w
 hipError_t launch_multidot(const double* V0, size_t vstride, int nv, const double* w, size_t n,
                            double* partial, int nblk, hipStream_t st, int norm_slot = -1);
-// w -= sum_i h[i] V_i, then partial[i * nblk + b] = block sums of V_i . w (nv entries)
-// and, when norm_slot >= 0, partial[norm_slot * nblk + b] = block sums of w . w
-hipError_t launch_axpy_dot(double* w, const double* V0, size_t vstride, int nv, const double* h,
-                           size_t n, bool want_dots, int norm_slot, double* partial, int nblk,
-                           hipStream_t st);
+// w -= sum_i h[i] V_i (h in device memory), partial[b] = block sums of the new w . w
+hipError_t launch_axpy_norm(double* w, const double* V0, size_t vstride, int nv, const double* h, size_t n,
+                            double* partial, int nblk, hipStream_t st);
 // out[i] = sum_b partial[i * nblk + b], i < k  (fixed order: deterministic)
 // row sums of partial (k rows of nblk) into out; also into host_out (a device
-// pointer to mapped coherent host memory) when it is not null.  With k == 1
-// and host_seq not null, the kernel then writes seq to *host_seq (mapped host
-// memory) after a system-scope fence, so a host that sees seq there also sees
-// every value written to host memory by this and earlier kernels.
+// pointer to mapped coherent host memory) when it is not null.  With host_seq
+// not null, the kernel then writes seq to *host_seq (mapped host memory) after a
+// system-scope fence, so a host that sees seq there also sees every value
+// written to host memory by this and earlier kernels.
 hipError_t launch_reduce_rows(const double* partial, int nblk, int k, double* out, hipStream_t st,
                               double* host_out = nullptr, unsigned* host_seq = nullptr, unsigned seq = 0);
 // dst = src / sqrt(*nrm2)
 hipError_t launch_scale_by_rnorm(double* dst, const double* src, size_t n, const double* nrm2,
                                  hipStream_t st);
-// dst = src * (1 / *beta)
-hipError_t launch_scale_by_rbeta(double* dst, const double* src, size_t n, const double* beta,
-                                 hipStream_t st);
-// x += sum_j y[j] Z_j  (k <= 8 per launch)
+// x += sum_j y[j] Z_j (y on the host, k <= kMaxRestart; n and zstride even, 16-byte aligned)
 hipError_t launch_update_x(double* x, const double* Z0, size_t zstride, int k, const double* y,
                            size_t n, hipStream_t st);
 // flexible GCR step (see k_gcr_step): coefficients by value, i <= kMaxRestart

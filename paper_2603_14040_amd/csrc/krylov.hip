@@ -28,90 +28,140 @@ int flat_blocks(size_t n) {
 namespace {
 
 constexpr int kNV = 8;
+// two neighbouring entries (vectors are 256-byte aligned and of even length)
+typedef double D2 __attribute__((ext_vector_type(2)));
 
+// Partial sums of V_i . w for NV vectors per block (those from blockIdx.y * NV on);
+// index nv stands for w . w where norm_slot asks for it.  How many vectors share a block
+// does not change a sum (a block's threads, their strides and the tree over them
+// are the same), only the work in flight: long vectors take 8 per block, so w is
+// read once for them; short ones one each, so that every vector's loads and its
+// reduction run side by side (up to 8 vectors of 25 500 entries: 4.4 us, against
+// 11 us with all of them in each block and a barrier pair per vector).  Long
+// vectors are bound by the reads of V (16 vectors of 3.35 M entries: 72 us, 6 TB/s).
+template <int NV>
 __global__ __launch_bounds__(256) void k_multidot(const double* __restrict__ V0, size_t vstride, int nv,
                                                  const double* __restrict__ w, size_t n,
                                                  double* __restrict__ partial, int nblk, int norm_slot) {
-    double acc[kNV];
+    __shared__ double part[4 * NV];
+    const int v0 = blockIdx.y * NV;
+    const double* V[NV];
 #pragma unroll
-    for (int v = 0; v < kNV; ++v) acc[v] = 0.0;
-    double nacc = 0.0;
-    for (size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x; t < n; t += (size_t)gridDim.x * blockDim.x) {
-        const double wv = w[t];
+    for (int v = 0; v < NV; ++v) V[v] = v0 + v < nv ? V0 + (v0 + v) * vstride : w;
+    double acc[NV];
 #pragma unroll
-        for (int v = 0; v < kNV; ++v)
-            if (v < nv) acc[v] += V0[v * vstride + t] * wv;
-        nacc += wv * wv;
-    }
+    for (int v = 0; v < NV; ++v) acc[v] = 0.0;
+    const size_t step = (size_t)gridDim.x * 256;
+    size_t t = blockIdx.x * (size_t)256 + threadIdx.x;
+    constexpr int U = NV >= 8 ? 2 : 8 / NV;          // entries in flight per thread
+    for (; t + (U - 1) * step < n; t += U * step) {
+        double x[U], y[U][NV];
 #pragma unroll
-    for (int v = 0; v < kNV; ++v) {
-        if (v < nv) {
-            const double s = block_sum(acc[v]);
-            if (threadIdx.x == 0) partial[(size_t)v * nblk + blockIdx.x] = s;
+        for (int u = 0; u < U; ++u) {
+            x[u] = w[t + u * step];
+#pragma unroll
+            for (int v = 0; v < NV; ++v) y[u][v] = V[v][t + u * step];
         }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int v = 0; v < NV; ++v) acc[v] += y[u][v] * x[u];
     }
-    if (norm_slot >= 0) {
-        const double s = block_sum(nacc);
-        if (threadIdx.x == 0) partial[(size_t)norm_slot * nblk + blockIdx.x] = s;
+    for (; t < n; t += step) {
+        const double x = w[t];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) acc[v] += V[v][t] * x;
     }
+    const double s = block_sums(acc, part);
+    const int v = v0 + threadIdx.x;
+    if (threadIdx.x < NV && (v < nv || (v == nv && norm_slot >= 0)))
+        partial[(size_t)(v < nv ? v : norm_slot) * nblk + blockIdx.x] = s;
 }
 
-__global__ __launch_bounds__(256) void k_axpy_dot(double* __restrict__ w, const double* __restrict__ V0,
-                                                 size_t vstride, int nv, const double* __restrict__ h, size_t n,
-                                                 int want_dots, int norm_slot, double* __restrict__ partial,
-                                                 int nblk) {
-    double hv[kNV];
-    double acc[kNV];
+// w -= sum_i h[i] V_i for any number of vectors, with the block sums of the new
+// w . w, in one pass over w (8 vectors' loads in flight at a time; a launch per 8
+// vectors re-read w and paid 5 us each on short vectors)
+__global__ __launch_bounds__(256) void k_axpy_norm(double* __restrict__ w, const double* __restrict__ V0,
+                                                  size_t vstride, int nv, const double* __restrict__ h, size_t n,
+                                                  double* __restrict__ partial) {
+    __shared__ double part[4];
+    double acc[1] = {0.0};
+    const size_t step = (size_t)gridDim.x * 256;
+    constexpr int U = 4;
+    for (size_t t0 = blockIdx.x * (size_t)256 + threadIdx.x; t0 < n; t0 += U * step) {
+        double x[U];
+        bool in[U];
 #pragma unroll
-    for (int v = 0; v < kNV; ++v) {
-        hv[v] = v < nv ? h[v] : 0.0;
-        acc[v] = 0.0;
-    }
-    double nacc = 0.0;
-    for (size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x; t < n; t += (size_t)gridDim.x * blockDim.x) {
-        double vv[kNV];
-        double x = w[t];
-#pragma unroll
-        for (int v = 0; v < kNV; ++v) {
-            vv[v] = v < nv ? V0[v * vstride + t] : 0.0;
-            x -= hv[v] * vv[v];
+        for (int u = 0; u < U; ++u) {
+            in[u] = t0 + u * step < n;
+            x[u] = in[u] ? w[t0 + u * step] : 0.0;
         }
-        w[t] = x;
-        if (want_dots) {
+        for (int v0 = 0; v0 < nv; v0 += kNV) {
+            double y[U][kNV];
 #pragma unroll
-            for (int v = 0; v < kNV; ++v) acc[v] += vv[v] * x;
-        }
-        nacc += x * x;
-    }
-    if (want_dots) {
+            for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int v = 0; v < kNV; ++v) {
-            if (v < nv) {
-                const double s = block_sum(acc[v]);
-                if (threadIdx.x == 0) partial[(size_t)v * nblk + blockIdx.x] = s;
+                for (int v = 0; v < kNV; ++v)
+                    y[u][v] = in[u] && v0 + v < nv ? V0[(v0 + v) * vstride + t0 + u * step] : 0.0;
+#pragma unroll
+            for (int v = 0; v < kNV; ++v) {
+                const double hv = v0 + v < nv ? h[v0 + v] : 0.0;
+#pragma unroll
+                for (int u = 0; u < U; ++u) x[u] -= hv * y[u][v];
             }
         }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (!in[u]) continue;
+            w[t0 + u * step] = x[u];
+            acc[0] += x[u] * x[u];
+        }
     }
-    if (norm_slot >= 0) {
-        const double s = block_sum(nacc);
-        if (threadIdx.x == 0) partial[(size_t)norm_slot * nblk + blockIdx.x] = s;
-    }
+    const double s = block_sums(acc, part);
+    if (threadIdx.x == 0) partial[blockIdx.x] = s;
 }
 
-__global__ __launch_bounds__(256) void k_reduce_rows(const double* __restrict__ partial, int nblk,
-                                                    double* __restrict__ out, double* __restrict__ host_out,
-                                                    unsigned* __restrict__ host_seq, unsigned seq) {
-    const double* row = partial + (size_t)blockIdx.x * nblk;
-    double s = 0.0;
-    for (int b = threadIdx.x; b < nblk; b += blockDim.x) s += row[b];
-    s = block_sum(s);
-    if (threadIdx.x == 0) {
-        out[blockIdx.x] = s;
-        if (host_out) host_out[blockIdx.x] = s;
-        if (host_seq) {
-            __threadfence_system();               // the values above reach host memory first
-            *(volatile unsigned*)host_seq = seq;
+// Row sums of partial (k rows of nblk) in one workgroup: 256 threads per row,
+// four rows at a time, each in the same fixed order.  The results go to out and,
+// where given, to mapped host memory, followed by the sequence number the host
+// polls (one launch where a workgroup per row needed a second one to post it).
+constexpr int kRowThreads = 256;
+constexpr int kRowGroups = 4;
+__global__ __launch_bounds__(kRowThreads * kRowGroups) void k_reduce_rows(
+    const double* __restrict__ partial, int nblk, int k, double* __restrict__ out, double* __restrict__ host_out,
+    unsigned* __restrict__ host_seq, unsigned seq) {
+    __shared__ double part[kRowGroups][kRowThreads / 64];
+    const int grp = threadIdx.x / kRowThreads, tid = threadIdx.x % kRowThreads;
+    for (int r0 = 0; r0 < k; r0 += kRowGroups) {
+        const int r = r0 + grp;
+        double s = 0.0;
+        if (r < k) {
+            const double* row = partial + (size_t)r * nblk;
+            constexpr int U = 8;
+            for (int b = tid; b < nblk; b += U * kRowThreads) {
+                double a[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) a[u] = b + u * kRowThreads < nblk ? row[b + u * kRowThreads] : 0.0;
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (b + u * kRowThreads < nblk) s += a[u];
+            }
         }
+        s = wave_sum(s);
+        if ((tid & 63) == 0) part[grp][tid >> 6] = s;
+        __syncthreads();
+        if (tid == 0 && r < k) {
+            double t = 0.0;
+            for (int q = 0; q < kRowThreads / 64; ++q) t += part[grp][q];
+            out[r] = t;
+            if (host_out) host_out[r] = t;
+        }
+        __syncthreads();
+    }
+    if (host_seq) {
+        __threadfence_system();                   // every thread's values reach host memory first
+        __syncthreads();
+        if (threadIdx.x == 0) *(volatile unsigned*)host_seq = seq;
     }
 }
 
@@ -122,24 +172,26 @@ __global__ __launch_bounds__(256) void k_scale_rnorm(double* __restrict__ dst, c
         dst[t] = src[t] * r;
 }
 
-__global__ __launch_bounds__(256) void k_scale_rbeta(double* __restrict__ dst, const double* __restrict__ src,
-                                                    size_t n, const double* __restrict__ beta) {
-    const double r = 1.0 / beta[0];
-    for (size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x; t < n; t += (size_t)gridDim.x * blockDim.x)
-        dst[t] = src[t] * r;
-}
-
-__global__ __launch_bounds__(256) void k_update_x(double* __restrict__ x, const double* __restrict__ Z0,
-                                                 size_t zstride, int k, const double* __restrict__ y, size_t n) {
-    double yv[kNV];
+// x += sum_i y[i] Z_i, the coefficients in the kernel arguments
+struct UpdateArgs {
+    double* x;
+    const double* Z0;
+    size_t stride, n;
+    int k;
+    double y[kMaxRestart];
+};
+__global__ __launch_bounds__(256) void k_update_x(const UpdateArgs a) {
+    for (size_t t = 2 * (blockIdx.x * (size_t)256 + threadIdx.x); t < a.n; t += (size_t)512 * gridDim.x) {
+        D2 x = *(const D2*)(a.x + t);
+        for (int v0 = 0; v0 < a.k; v0 += kNV) {
+            D2 z[kNV];
 #pragma unroll
-    for (int v = 0; v < kNV; ++v) yv[v] = v < k ? y[v] : 0.0;
-    for (size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x; t < n; t += (size_t)gridDim.x * blockDim.x) {
-        double s = x[t];
+            for (int v = 0; v < kNV; ++v)
+                z[v] = v0 + v < a.k ? *(const D2*)(a.Z0 + (v0 + v) * a.stride + t) : D2{0.0, 0.0};
 #pragma unroll
-        for (int v = 0; v < kNV; ++v)
-            if (v < k) s += yv[v] * Z0[v * zstride + t];
-        x[t] = s;
+            for (int v = 0; v < kNV; ++v) x += (v0 + v < a.k ? a.y[v0 + v] : 0.0) * z[v];
+        }
+        *(D2*)(a.x + t) = x;
     }
 }
 
@@ -149,22 +201,28 @@ __global__ __launch_bounds__(256) void k_update_x(double* __restrict__ x, const 
 // and, when z is given, z' = (z - sum_j hz_j Z_j) / nu, x += alpha z'.
 // The coefficients travel in the kernel arguments (uniform scalar loads).
 __global__ __launch_bounds__(256) void k_gcr_step(const GcrStepArgs a) {
-    for (size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x; t < a.n; t += (size_t)gridDim.x * blockDim.x) {
-        double wv = a.w[t];
-        if (a.orth_w) {
-#pragma unroll 4
-            for (int j = 0; j < a.i; ++j) wv -= a.hw[j] * a.W0[j * a.stride + t];
+    auto project = [&](D2 x, const double* h, const double* V0, size_t t) {
+        for (int v0 = 0; v0 < a.i; v0 += kNV) {
+            D2 y[kNV];
+#pragma unroll
+            for (int v = 0; v < kNV; ++v)
+                y[v] = v0 + v < a.i ? *(const D2*)(V0 + (v0 + v) * a.stride + t) : D2{0.0, 0.0};
+#pragma unroll
+            for (int v = 0; v < kNV; ++v) x -= (v0 + v < a.i ? h[v0 + v] : 0.0) * y[v];
         }
+        return x;
+    };
+    for (size_t t = 2 * (blockIdx.x * (size_t)256 + threadIdx.x); t < a.n; t += (size_t)512 * gridDim.x) {
+        D2 wv = *(const D2*)(a.w + t);
+        const D2 r = *(const D2*)(a.r + t);
+        if (a.orth_w) wv = project(wv, a.hw, a.W0, t);
         wv *= a.inv_nu;
-        a.w[t] = wv;
-        a.r[t] -= a.alpha * wv;
+        *(D2*)(a.w + t) = wv;
+        *(D2*)(a.r + t) = r - a.alpha * wv;
         if (a.z) {
-            double zv = a.z[t];
-#pragma unroll 4
-            for (int j = 0; j < a.i; ++j) zv -= a.hz[j] * a.Z0[j * a.stride + t];
-            zv *= a.inv_nu;
-            a.z[t] = zv;
-            a.x[t] += a.alpha * zv;
+            const D2 zv = project(*(const D2*)(a.z + t), a.hz, a.Z0, t) * a.inv_nu;
+            *(D2*)(a.z + t) = zv;
+            *(D2*)(a.x + t) = *(const D2*)(a.x + t) + a.alpha * zv;
         }
     }
 }
@@ -248,38 +306,28 @@ __global__ __launch_bounds__(256) void k_p_shift(Geom g, double* __restrict__ p,
 
 hipError_t launch_multidot(const double* V0, size_t vstride, int nv, const double* w, size_t n, double* partial,
                            int nblk, hipStream_t st, int norm_slot) {
-    for (int v0 = 0; v0 < nv; v0 += kNV) {
-        const int c = nv - v0 < kNV ? nv - v0 : kNV;
-        // the norm slot is an absolute row index; offset it for this chunk's partial base
-        const int ns = (v0 == 0 && norm_slot >= 0) ? norm_slot : -1;
-        hipLaunchKernelGGL(k_multidot, dim3(nblk), dim3(256), 0, st, V0 + v0 * vstride, vstride, c, w, n,
-                           partial + (size_t)v0 * nblk, nblk, ns);
-    }
+    const int rows = nv + (norm_slot >= 0 ? 1 : 0);
+    // vectors per block: 8 once the blocks of one group fill the chip by
+    // themselves (two per CU), fewer while they do not; nblk is n / 2048
+    const int per = nblk >= 512 ? 8 : nblk >= 128 ? 4 : 1;
+#define TPH_DOT(NV)                                                                                                    hipLaunchKernelGGL((k_multidot<NV>), dim3(nblk, (rows + NV - 1) / NV), dim3(256), 0, st, V0, vstride, nv, w, n,                        partial, nblk, norm_slot)
+    if (per == 8) TPH_DOT(8);
+    else if (per == 4) TPH_DOT(4);
+    else TPH_DOT(1);
+#undef TPH_DOT
     return hipGetLastError();
 }
 
-hipError_t launch_axpy_dot(double* w, const double* V0, size_t vstride, int nv, const double* h, size_t n,
-                           bool want_dots, int norm_slot, double* partial, int nblk, hipStream_t st) {
-    if (nv <= kNV) {
-        hipLaunchKernelGGL(k_axpy_dot, dim3(nblk), dim3(256), 0, st, w, V0, vstride, nv, h, n, want_dots ? 1 : 0,
-                           norm_slot, partial, nblk);
-        return hipGetLastError();
-    }
-    // more than kNV basis vectors: subtract in chunks, then one dot pass
-    for (int v0 = 0; v0 < nv; v0 += kNV) {
-        const int c = nv - v0 < kNV ? nv - v0 : kNV;
-        const bool last = v0 + c >= nv;
-        hipLaunchKernelGGL(k_axpy_dot, dim3(nblk), dim3(256), 0, st, w, V0 + v0 * vstride, vstride, c, h + v0, n, 0,
-                           last ? norm_slot : -1, partial, nblk);
-    }
-    if (want_dots) return launch_multidot(V0, vstride, nv, w, n, partial, nblk, st, -1);
+hipError_t launch_axpy_norm(double* w, const double* V0, size_t vstride, int nv, const double* h, size_t n,
+                            double* partial, int nblk, hipStream_t st) {
+    hipLaunchKernelGGL(k_axpy_norm, dim3(nblk), dim3(256), 0, st, w, V0, vstride, nv, h, n, partial);
     return hipGetLastError();
 }
 
 hipError_t launch_reduce_rows(const double* partial, int nblk, int k, double* out, hipStream_t st,
                               double* host_out, unsigned* host_seq, unsigned seq) {
-    if (host_seq && k != 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_reduce_rows, dim3(k), dim3(256), 0, st, partial, nblk, out, host_out, host_seq, seq);
+    hipLaunchKernelGGL(k_reduce_rows, dim3(1), dim3(kRowThreads * kRowGroups), 0, st, partial, nblk, k, out, host_out,
+                       host_seq, seq);
     return hipGetLastError();
 }
 
@@ -288,24 +336,25 @@ hipError_t launch_scale_by_rnorm(double* dst, const double* src, size_t n, const
     return hipGetLastError();
 }
 
-hipError_t launch_scale_by_rbeta(double* dst, const double* src, size_t n, const double* beta, hipStream_t st) {
-    hipLaunchKernelGGL(k_scale_rbeta, dim3(flat_blocks(n)), dim3(256), 0, st, dst, src, n, beta);
-    return hipGetLastError();
-}
-
 hipError_t launch_update_x(double* x, const double* Z0, size_t zstride, int k, const double* y, size_t n,
                            hipStream_t st) {
-    for (int v0 = 0; v0 < k; v0 += kNV) {
-        const int c = k - v0 < kNV ? k - v0 : kNV;
-        hipLaunchKernelGGL(k_update_x, dim3(flat_blocks(n)), dim3(256), 0, st, x, Z0 + v0 * zstride, zstride, c,
-                           y + v0, n);
-    }
+    if (k < 0 || k > kMaxRestart || (n & 1) || (zstride & 1)) return hipErrorInvalidValue;
+    UpdateArgs a{};
+    a.x = x;
+    a.Z0 = Z0;
+    a.stride = zstride;
+    a.n = n;
+    a.k = k;
+    for (int v = 0; v < k; ++v) a.y[v] = y[v];
+    const size_t b = (n + 511) / 512;
+    hipLaunchKernelGGL(k_update_x, dim3((unsigned)(b < 1 ? 1 : b > 2048 ? 2048 : b)), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 
 hipError_t launch_gcr_step(const GcrStepArgs& a, hipStream_t st) {
-    if (a.i < 0 || a.i > kMaxRestart) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_gcr_step, dim3(flat_blocks(a.n)), dim3(256), 0, st, a);
+    if (a.i < 0 || a.i > kMaxRestart || (a.n & 1) || (a.stride & 1)) return hipErrorInvalidValue;
+    const size_t b = (a.n + 511) / 512;
+    hipLaunchKernelGGL(k_gcr_step, dim3((unsigned)(b < 1 ? 1 : b > 2048 ? 2048 : b)), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 

@@ -56,8 +56,7 @@ void set_error(const std::string& m) { g_last_error = m; }
 constexpr int kSlotH1 = 0;                        // kMaxRestart + 1 entries
 constexpr int kSlotH2 = kSlotH1 + kMaxRestart + 1;
 constexpr int kSlotNrm = kSlotH2 + kMaxRestart + 1;
-constexpr int kSlotY = kSlotNrm + 1;              // kMaxRestart entries
-constexpr int kSlotMisc = kSlotY + kMaxRestart;   // 8 entries
+constexpr int kSlotMisc = kSlotNrm + 1;           // 8 entries
 constexpr int kScalars = kSlotMisc + 8;
 
 struct LevelBuf {
@@ -722,8 +721,8 @@ tph_status precondition(tph_solver* s, double* vraw, double* zraw, bool energy, 
 
 // reduce partial rows into `k` device scalars at slot; with to_host the same
 // kernel also writes them into the mapped host mirror (no copy launch).  A
-// reduction with `signal` (k == 1) ends the values the host is about to read:
-// it also posts the next sequence number, which wait_signal() polls.
+// reduction with `signal` ends the values the host is about to read: it also
+// posts the next sequence number, which wait_signal() polls.
 tph_status reduce_to(tph_solver* s, int nblk, int k, int slot, bool to_host = false, bool signal = false) {
     TPH_HIP(launch_reduce_rows(s->partial, nblk, k, s->dscal + slot, s->st, to_host ? s->hscal_dev + slot : nullptr,
                                signal ? s->hseq_dev : nullptr, signal ? ++s->seq : 0u));
@@ -898,8 +897,7 @@ tph_status fgmres(tph_solver* s, double* braw, tph_info* info) {
             // 1/sqrt(2) of its value before the projection (cancellation)
             TPH_HIP(launch_multidot(Vk(0), n3, j + 1, w, n3, s->partial, nblk_flat, s->st, j + 1));
             TPH_TRY(reduce_to(s, nblk_flat, j + 2, kSlotH1, true));  // h (j+1) and |w|^2 at kSlotH1 + j + 1
-            TPH_HIP(launch_axpy_dot(w, Vk(0), n3, j + 1, s->dscal + kSlotH1, n3, false, 0, s->partial, nblk_flat,
-                                    s->st));
+            TPH_HIP(launch_axpy_norm(w, Vk(0), n3, j + 1, s->dscal + kSlotH1, n3, s->partial, nblk_flat, s->st));
             TPH_TRY(reduce_to(s, nblk_flat, 1, kSlotNrm, true, true));
             TPH_TRY(wait_signal(s));
             double* col = &H[(size_t)j * (m + 1)];
@@ -908,8 +906,7 @@ tph_status fgmres(tph_solver* s, double* braw, tph_info* info) {
             if (s->hscal[kSlotNrm] < 0.5 * w2_before) {
                 TPH_HIP(launch_multidot(Vk(0), n3, j + 1, w, n3, s->partial, nblk_flat, s->st));
                 TPH_TRY(reduce_to(s, nblk_flat, j + 1, kSlotH2, true));
-                TPH_HIP(launch_axpy_dot(w, Vk(0), n3, j + 1, s->dscal + kSlotH2, n3, false, 0, s->partial, nblk_flat,
-                                        s->st));
+                TPH_HIP(launch_axpy_norm(w, Vk(0), n3, j + 1, s->dscal + kSlotH2, n3, s->partial, nblk_flat, s->st));
                 TPH_TRY(reduce_to(s, nblk_flat, 1, kSlotNrm, true, true));
                 TPH_TRY(wait_signal(s));
                 for (int i = 0; i <= j; ++i) col[i] += s->hscal[kSlotH2 + i];
@@ -943,8 +940,7 @@ tph_status fgmres(tph_solver* s, double* braw, tph_info* info) {
             for (int k = i + 1; k < jdone; ++k) t -= H[(size_t)k * (m + 1) + i] * y[k];
             y[i] = t / H[(size_t)i * (m + 1) + i];
         }
-        TPH_HIP(hipMemcpyAsync(s->dscal + kSlotY, y.data(), jdone * sizeof(double), hipMemcpyHostToDevice, s->st));
-        TPH_HIP(launch_update_x(s->x, s->Z, n3, jdone, s->dscal + kSlotY, n3, s->st));
+        TPH_HIP(launch_update_x(s->x, s->Z, n3, jdone, y.data(), n3, s->st));
     }
     TPH_TRY(remove_pressure_mean(s, s->x));
     TPH_HIP(hipStreamSynchronize(s->st));
@@ -1039,8 +1035,7 @@ tph_status gcr(tph_solver* s, double* braw, tph_info* info) {
             TPH_TRY(precondition(s, Vk(0), z, true, w));
             // <r, w>, <w_j, w> (j < i) and |w|^2 in one pass
             TPH_HIP(launch_multidot(Vk(0), n3, i + 1, w, n3, s->partial, nblk, s->st, i + 1));
-            TPH_TRY(reduce_to(s, nblk, i + 2, kSlotH1, true));
-            TPH_HIP(launch_post_seq(s->hseq_dev, ++s->seq, s->st));
+            TPH_TRY(reduce_to(s, nblk, i + 2, kSlotH1, true, true));
             TPH_TRY(wait_signal(s));
             const double c = s->hscal[kSlotH1];
             const double w2 = s->hscal[kSlotH1 + i + 1];
@@ -1052,16 +1047,14 @@ tph_status gcr(tph_solver* s, double* braw, tph_info* info) {
             double nu2 = w2 - h2;
             a.orth_w = 1;
             if (i > 0 && !(nu2 >= kCgsTrust * w2)) {
-                TPH_HIP(launch_axpy_dot(w, Vk(1), n3, i, s->dscal + kSlotH1 + 1, n3, false, 0, s->partial, nblk,
-                                        s->st));
+                TPH_HIP(launch_axpy_norm(w, Vk(1), n3, i, s->dscal + kSlotH1 + 1, n3, s->partial, nblk, s->st));
                 TPH_TRY(reduce_to(s, nblk, 1, kSlotNrm, true, true));
                 TPH_TRY(wait_signal(s));
                 nu2 = s->hscal[kSlotNrm];
                 if (nu2 < 0.5 * w2) {
                     TPH_HIP(launch_multidot(Vk(1), n3, i, w, n3, s->partial, nblk, s->st));
                     TPH_TRY(reduce_to(s, nblk, i, kSlotH2, true));
-                    TPH_HIP(launch_axpy_dot(w, Vk(1), n3, i, s->dscal + kSlotH2, n3, false, 0, s->partial, nblk,
-                                            s->st));
+                    TPH_HIP(launch_axpy_norm(w, Vk(1), n3, i, s->dscal + kSlotH2, n3, s->partial, nblk, s->st));
                     TPH_TRY(reduce_to(s, nblk, 1, kSlotNrm, true, true));
                     TPH_TRY(wait_signal(s));
                     for (int j = 0; j < i; ++j) a.hz[j] += s->hscal[kSlotH2 + j];
@@ -1122,9 +1115,7 @@ tph_status gcr(tph_solver* s, double* braw, tph_info* info) {
                 for (int i = k; i < done; ++i) t += C[(size_t)i * m + k] * alph[i];
                 ycoef[k] = t;
             }
-            TPH_HIP(hipMemcpyAsync(s->dscal + kSlotY, ycoef.data(), done * sizeof(double), hipMemcpyHostToDevice,
-                                   s->st));
-            TPH_HIP(launch_update_x(s->x, s->Z, n3, done, s->dscal + kSlotY, n3, s->st));
+            TPH_HIP(launch_update_x(s->x, s->Z, n3, done, ycoef.data(), n3, s->st));
         }
     }
     TPH_TRY(remove_pressure_mean(s, s->x));
