@@ -27,6 +27,7 @@
 #include "../../include/tephra.h"
 #include "devmem.h"
 #include "fused_dev.h"
+#include "tail_dev.h"
 #include "solver_internal.h"
 #include "stencil_dev.h"
 
@@ -145,11 +146,12 @@ __global__ __launch_bounds__(kRRTileW * rr_tile_h<T>()) void kb_res_restrict(con
                                                    it.y & 0xffff, it.y >> 16);
 }
 
-template <typename T>
-__global__ __launch_bounds__(coarse_threads<T>()) void kb_coarse(const CoarseArgs<T>* __restrict__ args,
-                                                                const int* __restrict__ active) {
+// NT x KP covers the largest tail of the batch
+template <typename T, int NT, int KP>
+__global__ __launch_bounds__(NT) void kb_coarse(const CoarseArgs<T>* __restrict__ args,
+                                                const int* __restrict__ active) {
     if (!active[blockIdx.x]) return;
-    coarse_cycle_body<T>(args[blockIdx.x]);
+    coarse_cycle_body<T, NT, KP>(args[blockIdx.x]);
 }
 
 // ---------------------------------------------------- finest-level cell kernels
@@ -402,6 +404,7 @@ struct tph_batch {
     void* d_lev = nullptr;                         // BLevel<T>[count * kMaxLevels]
     BProb* d_prob = nullptr;
     void* d_cargs = nullptr;                       // CoarseArgs<T>[count]
+    TailShape tail{256, 1};                        // covers the largest coarse tail of the batch
     size_t coarse_lds = 0;
     int* d_active = nullptr;                       // iteration mask
     int* d_reorth = nullptr;                       // per problem: second Gram-Schmidt pass this iteration
@@ -491,6 +494,16 @@ tph_status join_problems(tph_batch* b) {
     return TPH_OK;
 }
 
+// the batched tail kernel of a shape of coarse_cycle_shape
+template <typename T>
+const void* tail_kernel(const TailShape& t) {
+    if (t.threads == 256) return (const void*)kb_coarse<T, 256, 1>;
+    if (t.pairs == 1) return (const void*)kb_coarse<T, 512, 1>;
+    if constexpr (sizeof(T) == 4)
+        if (t.pairs == 4) return (const void*)kb_coarse<T, 512, 4>;
+    return (const void*)kb_coarse<T, 512, 2>;
+}
+
 template <typename T>
 tph_status build_tables_t(tph_batch* b) {
     const int P = b->count;
@@ -518,7 +531,7 @@ tph_status build_tables_t(tph_batch* b) {
         a.smoother = b->d.smoother;
         a.omega = (T)b->d.omega;
         for (int q = 0; q < a.nl; ++q) {
-            a.g[q] = v.g[v.lc + q];
+            a.lv[q] = tail_level<T>(v.g[v.lc + q]);
             a.eb[q] = (const T*)v.eb[v.lc + q];
             a.ep[q] = (const T*)v.ep[v.lc + q];
             a.nu_pre[q] = v.nu_pre[v.lc + q];
@@ -530,14 +543,16 @@ tph_status build_tables_t(tph_batch* b) {
         a.ey = (T*)v.ey[v.lc][0];
         a.Minv = v.Minv;
         lds = std::max(lds, v.lc_lds);
+        const TailShape sh = coarse_cycle_shape(a.lv[0].nx, a.lv[0].ny);
+        if (sh.threads * sh.pairs > b->tail.threads * b->tail.pairs) b->tail = sh;
     }
     B_TRY(b_alloc(b, &b->d_lev, lev.size() * sizeof(BLevel<T>)));
     B_HIP(hipMemcpy(b->d_lev, lev.data(), lev.size() * sizeof(BLevel<T>), hipMemcpyHostToDevice));
     B_TRY(b_alloc(b, &b->d_cargs, ca.size() * sizeof(CoarseArgs<T>)));
     B_HIP(hipMemcpy(b->d_cargs, ca.data(), ca.size() * sizeof(CoarseArgs<T>), hipMemcpyHostToDevice));
     b->coarse_lds = lds;
-    if (lds > 64 * 1024)
-        B_HIP(hipFuncSetAttribute((const void*)kb_coarse<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    if (lds > 64 * 1024) B_HIP(hipFuncSetAttribute(tail_kernel<T>(b->tail), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                   (int)lds));
     return TPH_OK;
 }
 
@@ -632,8 +647,10 @@ tph_status enqueue_iteration_t(tph_batch* b) {
             hipLaunchKernelGGL(kb_res_restrict<T>, dim3(b->itn_rr[d]), dim3(kRRTileW * rr_tile_h<T>()), 0, st, lev,
                                b->it_rr[d], act, d, cur);
         }
-        hipLaunchKernelGGL(kb_coarse<T>, dim3(b->count), dim3(coarse_threads<T>()), b->coarse_lds, st,
-                           (const CoarseArgs<T>*)b->d_cargs, act);
+        {
+            void* args[] = {(void*)&b->d_cargs, (void*)&act};
+            B_HIP(hipLaunchKernel(tail_kernel<T>(b->tail), dim3(b->count), dim3(b->tail.threads), args, b->coarse_lds, st));
+        }
         for (int d = b->maxdepth - 1; d >= 0; --d) {
             if (b->itn_tiles[d] == 0) continue;
             int cur = cur_pre[d];

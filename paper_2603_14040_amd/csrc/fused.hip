@@ -4,6 +4,7 @@
 #include <hip/hip_ext.h>
 
 #include "fused_dev.h"
+#include "tail_dev.h"
 
 namespace tph {
 namespace {
@@ -33,9 +34,35 @@ __global__ __launch_bounds__(CTW * CTH) void k_res_restrict(Geom g, Geom gc, con
     res_restrict_body<T, CTW, CTH>(g, gc, ex, ey, rx, ry, eb, ep, rcx, rcy, tbx, tby);
 }
 
-template <typename T>
-__global__ __launch_bounds__(coarse_threads<T>()) void k_coarse_cycle(CoarseArgs<T> A) {
-    coarse_cycle_body<T>(A);
+template <typename T, int NT, int KP>
+__global__ __launch_bounds__(NT) void k_coarse_cycle(CoarseArgs<T> A) {
+    coarse_cycle_body<T, NT, KP>(A);
+}
+
+// One launch; the kernel's dynamic LDS limit is raised when a launch needs
+// more than 64 KB.  The attribute is per function (and device), so it is set
+// only when a launch needs more than any earlier one on this device.
+template <typename T, int NT, int KP>
+hipError_t launch_tail(const CoarseArgs<T>& a, size_t lds_bytes, hipStream_t st) {
+    static thread_local int dev_cached = -1;
+    static thread_local size_t granted = 64 * 1024;
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return hipGetLastError();
+    if (dev != dev_cached) {
+        dev_cached = dev;
+        granted = 64 * 1024;
+    }
+    if (lds_bytes > granted) {
+        const hipError_t e = hipFuncSetAttribute((const void*)k_coarse_cycle<T, NT, KP>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();   // do not leave the error pending for unrelated later launches
+            return e;
+        }
+        granted = lds_bytes;
+    }
+    hipLaunchKernelGGL((k_coarse_cycle<T, NT, KP>), dim3(1), dim3(NT), lds_bytes, st, a);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -43,12 +70,17 @@ __global__ __launch_bounds__(coarse_threads<T>()) void k_coarse_cycle(CoarseArgs
 
 template <typename T>
 size_t coarse_cycle_lds_bytes(const Geom* g, int nl, int nc) {
-    size_t n = 0;
-    for (int l = 0; l < nl; ++l) n += 6 * (size_t)(g[l].ny + 2) * (g[l].nx + 2);
-    n += 2 * (size_t)(g[0].ny + 2) * (g[0].nx + 2);
-    size_t bytes = n * sizeof(T);
-    bytes = (bytes + 7) / 8 * 8 + (size_t)nc * sizeof(double);
-    return bytes;
+    size_t n = dev::tail_area<T>(g[0].nx, g[0].ny) + 16;
+    for (int l = 1; l < nl; ++l) n += (l < nl - 1 ? 3 : 1) * dev::tail_area<T>(g[l].nx, g[l].ny);
+    return n + (size_t)dev::tail_dense_pad(nc) * sizeof(double);
+}
+
+// as few threads as own the top level's cell pairs one each (fewer waves meet
+// at every barrier); two pairs per thread beyond 1024
+TailShape coarse_cycle_shape(int nx, int ny) {
+    const int pairs = (nx / 2) * ny;
+    if (pairs <= 256) return {256, 1};
+    return {512, pairs <= 512 ? 1 : pairs <= 1024 ? 2 : 4};
 }
 
 template <typename T>
@@ -91,30 +123,15 @@ hipError_t launch_res_restrict(const Geom& gf, const Geom& gc, const T* ex, cons
 }
 
 template <typename T>
-hipError_t launch_coarse_cycle(const CoarseArgs<T>& a, size_t lds_bytes, int max_lds, hipStream_t st) {
-    // raise the kernel's dynamic LDS limit when a launch needs more than 64 KB;
-    // the attribute is per function (and device), so it is set only when a
-    // launch needs more than any earlier one on this device
-    (void)max_lds;
-    static thread_local int dev_cached = -1;
-    static thread_local size_t granted = 64 * 1024;
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return hipGetLastError();
-    if (dev != dev_cached) {
-        dev_cached = dev;
-        granted = 64 * 1024;
-    }
-    if (lds_bytes > granted) {
-        hipError_t e = hipFuncSetAttribute((const void*)k_coarse_cycle<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)lds_bytes);
-        if (e != hipSuccess) {
-            (void)hipGetLastError();   // do not leave the error pending for unrelated later launches
-            return e;
-        }
-        granted = lds_bytes;
-    }
-    hipLaunchKernelGGL(k_coarse_cycle<T>, dim3(1), dim3(coarse_threads<T>()), lds_bytes, st, a);
-    return hipGetLastError();
+hipError_t launch_coarse_cycle(const CoarseArgs<T>& a, size_t lds_bytes, hipStream_t st) {
+    const TailShape sh = coarse_cycle_shape(a.lv[0].nx, a.lv[0].ny);
+    if ((a.lv[0].nx / 2) * a.lv[0].ny > sh.threads * sh.pairs) return hipErrorInvalidValue;
+    if (sh.threads == 256) return launch_tail<T, 256, 1>(a, lds_bytes, st);
+    if (sh.pairs == 1) return launch_tail<T, 512, 1>(a, lds_bytes, st);
+    if (sh.pairs == 2) return launch_tail<T, 512, 2>(a, lds_bytes, st);
+    // a FP64 tail of more than 2048 cells does not fit the LDS
+    if constexpr (sizeof(T) == 4) return launch_tail<T, 512, 4>(a, lds_bytes, st);
+    else return hipErrorInvalidValue;
 }
 
 #define TPH_INST(T)                                                                                                \
@@ -124,7 +141,7 @@ hipError_t launch_coarse_cycle(const CoarseArgs<T>& a, size_t lds_bytes, int max
                                               hipStream_t, hipEvent_t, hipEvent_t);                                 \
     template hipError_t launch_res_restrict<T>(const Geom&, const Geom&, const T*, const T*, const T*, const T*,    \
                                                const T*, const T*, T*, T*, hipStream_t);                            \
-    template hipError_t launch_coarse_cycle<T>(const CoarseArgs<T>&, size_t, int, hipStream_t);
+    template hipError_t launch_coarse_cycle<T>(const CoarseArgs<T>&, size_t, hipStream_t);
 TPH_INST(float)
 TPH_INST(double)
 #undef TPH_INST

@@ -18,9 +18,6 @@
 //   coarse cells, kept in LDS, then the normalised restriction (gather form
 //   of Alg. "4-Color Parallel Restriction"); the fine residual never goes
 //   to memory.
-// coarse_cycle_body: the V-cycle on every level from a small level down to
-//   the coarsest in one workgroup, all fields resident in LDS, ending in the
-//   FP64 dense solve.
 #pragma once
 #include "kernels.h"
 #include "reduce.h"
@@ -607,417 +604,6 @@ __device__ __forceinline__ void res_restrict_body(const Geom& g, const Geom& gc,
     const int I = I0 + tid / CTW, J = J0 + (tid - (tid / CTW) * CTW);
     if (I > gc.ny || J > gc.nx) return;
     restrict_cell<T, RC>(g, gc, stx, sty, fi0, fj0, I, J, rcx, rcy);
-}
-
-// ---------------------------------------------------------------------------
-// coarse tail of the V-cycle in one workgroup
-// ---------------------------------------------------------------------------
-template <typename T>
-struct LGeo {            // a level inside LDS: tight pitch nx + 2
-    int nx, ny, P;
-    T idx, idy, idx2, idy2;
-};
-
-// Loops of the coarse tail map threads to rows: 2^s consecutive threads
-// share a row, with 2^s the smallest power of two covering the row (at most
-// 64), so every lane of a wave has work on small levels and node indices come
-// from shifts instead of divisions by a runtime width.
-__device__ __forceinline__ int lanes_log2(int width) {
-    const int s = width <= 1 ? 0 : 32 - __clz(width - 1);
-    return s < 6 ? s : 6;
-}
-
-// one Gauss-Seidel colour half-sweep of component comp, in place
-template <typename T>
-__device__ void cc_gs_half(const LGeo<T>& L, const LevelC<T>& k, int comp, int col, T* ex, T* ey, const T* rx,
-                           const T* ry, const T* eb, const T* ep, T omega) {
-    const int ncol = comp == 0 ? L.nx - 1 : L.nx;
-    const int nrow = comp == 0 ? L.ny : L.ny - 1;
-    const int tid = threadIdx.x;
-    const int ls = lanes_log2((ncol + 1) >> 1);          // lanes per row: one node of the colour each
-    const int lm = (1 << ls) - 1;
-    for (int i = 1 + (tid >> ls); i <= nrow; i += blockDim.x >> ls) {
-        // first column of colour col in row i: (i + j) & 1 == col
-        const int j0 = 1 + (((i + 1) & 1) != col ? 1 : 0);
-        for (int j = j0 + 2 * (tid & lm); j <= ncol; j += 2 << ls) {
-            const int c = i * L.P + j;
-            if (comp == 0) {
-                const T d = lx_diag(eb, ep, c, L.P, i, L.ny, k);
-                const T e = relax(ex[c], omega, rx[c] - lx_row(ex, ey, eb, ep, c, L.P, k.idx, k.idy), d);
-                ex[c] = e;
-                if (i == 1) ex[c - L.P] = k.mirS * e;
-                if (i == L.ny) ex[c + L.P] = k.mirN * e;
-            } else {
-                const T d = ly_diag(eb, ep, c, L.P, j, L.nx, k);
-                const T e = relax(ey[c], omega, ry[c] - ly_row(ex, ey, eb, ep, c, L.P, k.idx, k.idy), d);
-                ey[c] = e;
-                if (j == 1) ey[c - 1] = k.mirW * e;
-                if (j == L.nx) ey[c + 1] = k.mirE * e;
-            }
-        }
-    }
-}
-
-// Jacobi sweep in place: new values held in registers across a barrier.
-// Flat mapping over the level's nx * ny nodes: the coarse tail holds at most
-// 64 x 64 cells, so a thread owns at most 4096 / blockDim.x <= KMAX nodes.
-template <typename T>
-__device__ void cc_jacobi(const LGeo<T>& L, const LevelC<T>& k, T* ex, T* ey, const T* rx, const T* ry,
-                          const T* eb, const T* ep, T omega) {
-    constexpr int KMAX = 8;
-    T nvx[KMAX], nvy[KMAX];
-    const int n = L.ny * L.nx;
-    int t = 0;
-    for (int q = threadIdx.x; q < n && t < KMAX; q += blockDim.x, ++t) {
-        const int i = 1 + q / L.nx, j = 1 + (q - (q / L.nx) * L.nx);
-        const int c = i * L.P + j;
-        nvx[t] = (j < L.nx) ? relax(ex[c], omega, rx[c] - lx_row(ex, ey, eb, ep, c, L.P, k.idx, k.idy),
-                                    lx_diag(eb, ep, c, L.P, i, L.ny, k))
-                            : (T)0;
-        nvy[t] = (i < L.ny) ? relax(ey[c], omega, ry[c] - ly_row(ex, ey, eb, ep, c, L.P, k.idx, k.idy),
-                                    ly_diag(eb, ep, c, L.P, j, L.nx, k))
-                            : (T)0;
-    }
-    __syncthreads();
-    t = 0;
-    for (int q = threadIdx.x; q < n && t < KMAX; q += blockDim.x, ++t) {
-        const int i = 1 + q / L.nx, j = 1 + (q - (q / L.nx) * L.nx);
-        const int c = i * L.P + j;
-        if (j < L.nx) {
-            ex[c] = nvx[t];
-            if (i == 1) ex[c - L.P] = k.mirS * nvx[t];
-            if (i == L.ny) ex[c + L.P] = k.mirN * nvx[t];
-        }
-        if (i < L.ny) {
-            ey[c] = nvy[t];
-            if (j == 1) ey[c - 1] = k.mirW * nvy[t];
-            if (j == L.nx) ey[c + 1] = k.mirE * nvy[t];
-        }
-    }
-    __syncthreads();
-}
-
-template <typename T>
-constexpr int coarse_threads() { return sizeof(T) == 4 ? 1024 : 512; }
-
-template <typename T>
-__device__ __forceinline__ void coarse_cycle_body(const CoarseArgs<T>& A) {
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    T* sm = (T*)smem_raw;
-    const int nl = A.nl;
-    // per-level tables live in LDS (not in per-lane arrays, which would go
-    // to scratch when indexed by the level number)
-    __shared__ LGeo<T> L[kMaxLevels];
-    __shared__ LevelC<T> K[kMaxLevels];
-    __shared__ int foff[kMaxLevels];
-    __shared__ int s_top_off;
-    const int tid = threadIdx.x, nthr = blockDim.x;
-    // row-parallel mapping for a row of `w` entries: (row, column, row stride, column stride)
-    auto rowmap = [&](int w, int& r0, int& rstep, int& c0, int& cstep) {
-        const int ls = lanes_log2(w);
-        r0 = tid >> ls;
-        rstep = nthr >> ls;
-        c0 = tid & ((1 << ls) - 1);
-        cstep = 1 << ls;
-    };
-    // Small coarsest systems (at most 128 unknowns, RM rows per 16-lane
-    // group): each lane's entries of the inverse are loaded into registers
-    // first, so their memory latency hides behind the load phase below
-    // instead of stalling the coarsest solve.  Same products and sums in the
-    // same order as the loop over memory.
-    constexpr int KM = 8, RM = sizeof(T) == 4 ? 2 : 4;
-    const int sub = tid & 15, grp = tid >> 4, ngrp = nthr >> 4;
-    const bool minv_regs = A.nc <= 16 * KM && A.nc <= RM * ngrp;
-    double mv[RM][KM];
-    if (minv_regs) {
-#pragma unroll
-        for (int r = 0; r < RM; ++r) {
-            const int m = grp + r * ngrp;
-#pragma unroll
-            for (int k = 0; k < KM; ++k) {
-                const int q = sub + 16 * k;
-                mv[r][k] = (m < A.nc && q < A.nc) ? A.Minv[(size_t)m * A.nc + q] : 0.0;
-            }
-        }
-    }
-    if (tid == 0) {
-        int off = 0;
-        for (int l = 0; l < nl; ++l) {
-            L[l].nx = A.g[l].nx;
-            L[l].ny = A.g[l].ny;
-            L[l].P = A.g[l].nx + 2;
-            K[l] = level_consts<T>(A.g[l]);
-            foff[l] = off;
-            off += 6 * (L[l].ny + 2) * L[l].P;
-        }
-        s_top_off = off;
-    }
-    __syncthreads();
-    // field q of level l: ex, ey, rx, ry, eb, ep
-    auto F = [&](int l, int q) -> T* { return sm + foff[l] + q * (L[l].ny + 2) * L[l].P; };
-    const int ntop = (L[0].ny + 2) * L[0].P;
-    T* tx = sm + s_top_off;
-    T* ty = tx + ntop;
-    const size_t off_end = (size_t)s_top_off + 2 * (size_t)ntop;
-    double* rs = (double*)(sm + ((off_end * sizeof(T) + 7) / 8) * 8 / sizeof(T));
-
-    // load viscosities of every level and the right-hand side of the top level; zero the rest.
-    // One flat index over all levels; the first KL entries of every thread are
-    // loaded into registers together (all loads in flight) before any store.
-    __shared__ int qoff[kMaxLevels + 1];
-    if (tid == 0) {
-        int q = 0;
-        for (int l = 0; l < nl; ++l) {
-            qoff[l] = q;
-            q += (L[l].ny + 2) * L[l].P;
-        }
-        qoff[nl] = q;
-    }
-    __syncthreads();
-    {
-        constexpr int KL = sizeof(T) == 4 ? 8 : 16;
-        const int ntot = qoff[nl];
-        auto locate = [&](int q, int& l, int& i, int& j) {
-            l = 0;
-            while (q >= qoff[l + 1]) ++l;
-            const int r = q - qoff[l];
-            i = r / L[l].P;
-            j = r - i * L[l].P;
-        };
-        T vb[KL], vp[KL], vx[KL], vy[KL];
-#pragma unroll
-        for (int k = 0; k < KL; ++k) {
-            const int q = tid + k * nthr;
-            vb[k] = vp[k] = vx[k] = vy[k] = (T)0;
-            if (q < ntot) {
-                int l, i, j;
-                locate(q, l, i, j);
-                const int cg = i * A.g[l].pitch + j;
-                vb[k] = A.eb[l][cg];
-                vp[k] = A.ep[l][cg];
-                if (l == 0) {
-                    vx[k] = A.rx[cg];
-                    vy[k] = A.ry[cg];
-                }
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < KL; ++k) {
-            const int q = tid + k * nthr;
-            if (q < ntot) {
-                int l, i, j;
-                locate(q, l, i, j);
-                const int r = i * L[l].P + j;
-                F(l, 0)[r] = (T)0;
-                F(l, 1)[r] = (T)0;
-                F(l, 2)[r] = vx[k];
-                F(l, 3)[r] = vy[k];
-                F(l, 4)[r] = vb[k];
-                F(l, 5)[r] = vp[k];
-            }
-        }
-        // remaining entries (only for very elongated tails)
-        for (int q = tid + KL * nthr; q < ntot; q += nthr) {
-            int l, i, j;
-            locate(q, l, i, j);
-            const int r = i * L[l].P + j, cg = i * A.g[l].pitch + j;
-            F(l, 0)[r] = (T)0;
-            F(l, 1)[r] = (T)0;
-            F(l, 2)[r] = l == 0 ? A.rx[cg] : (T)0;
-            F(l, 3)[r] = l == 0 ? A.ry[cg] : (T)0;
-            F(l, 4)[r] = A.eb[l][cg];
-            F(l, 5)[r] = A.ep[l][cg];
-        }
-    }
-    __syncthreads();
-
-    // The level tables are read from LDS once per level and phase group into
-    // registers (the colour phases then start without an LDS round trip).
-    auto smooth = [&](int l, int nu) {
-        T *ex = F(l, 0), *ey = F(l, 1), *rx = F(l, 2), *ry = F(l, 3), *eb = F(l, 4), *ep = F(l, 5);
-        const LGeo<T> Lg = L[l];
-        const LevelC<T> Kg = K[l];
-        for (int s = 0; s < nu; ++s) {
-            if (A.smoother == kSmGS) {
-                for (int h = 0; h < 4; ++h) {
-                    cc_gs_half(Lg, Kg, h >> 1, h & 1, ex, ey, rx, ry, eb, ep, A.omega);
-                    __syncthreads();
-                }
-            } else {
-                cc_jacobi(Lg, Kg, ex, ey, rx, ry, eb, ep, A.omega);
-            }
-        }
-    };
-
-    // ---- down: smooth, residual, restrict
-    for (int l = 0; l < nl - 1; ++l) {
-        smooth(l, A.nu_pre[l]);
-        const LGeo<T> G = L[l];
-        const LevelC<T> Kl = K[l];
-        T *ex = F(l, 0), *ey = F(l, 1), *rx = F(l, 2), *ry = F(l, 3), *eb = F(l, 4), *ep = F(l, 5);
-        int rt, rs_, ct, cs_;
-        rowmap(G.P, rt, rs_, ct, cs_);
-        for (int i = rt; i < G.ny + 2; i += rs_) {
-            for (int j = ct; j < G.P; j += cs_) {
-                const int q = i * G.P + j;
-                const bool vx = i >= 1 && i <= G.ny && j >= 1 && j < G.nx;
-                const bool vy = i >= 1 && i < G.ny && j >= 1 && j <= G.nx;
-                tx[q] = vx ? rx[q] - lx_row(ex, ey, eb, ep, q, G.P, Kl.idx, Kl.idy) : (T)0;
-                ty[q] = vy ? ry[q] - ly_row(ex, ey, eb, ep, q, G.P, Kl.idx, Kl.idy) : (T)0;
-            }
-        }
-        __syncthreads();
-        const LGeo<T> C = L[l + 1];
-        T *rcx = F(l + 1, 2), *rcy = F(l + 1, 3);
-        rowmap(C.nx, rt, rs_, ct, cs_);
-        for (int I = 1 + rt; I <= C.ny; I += rs_) {
-            for (int J = 1 + ct; J <= C.nx; J += cs_) {
-                const int Cc = I * C.P + J;
-                if (J < C.nx) {
-                    T s = (T)0, wy = (T)0;
-                    for (int a4 = 0; a4 < 4; ++a4) {
-                        const int i = 2 * I - 2 + a4;
-                        if (i < 1 || i > G.ny) continue;
-                        const T w = (a4 == 1 || a4 == 2) ? (T)0.75 : (T)0.25;
-                        const int c = i * G.P + 2 * J;
-                        s += w * ((T)0.5 * tx[c - 1] + tx[c] + (T)0.5 * tx[c + 1]);
-                        wy += w;
-                    }
-                    rcx[Cc] = s / ((T)2 * wy);
-                }
-                if (I < C.ny) {
-                    T s = (T)0, wx = (T)0;
-                    for (int b4 = 0; b4 < 4; ++b4) {
-                        const int j = 2 * J - 2 + b4;
-                        if (j < 1 || j > G.nx) continue;
-                        const T w = (b4 == 1 || b4 == 2) ? (T)0.75 : (T)0.25;
-                        const int c = 2 * I * G.P + j;
-                        s += w * ((T)0.5 * ty[c - G.P] + ty[c] + (T)0.5 * ty[c + G.P]);
-                        wx += w;
-                    }
-                    rcy[Cc] = s / ((T)2 * wx);
-                }
-            }
-        }
-        __syncthreads();
-    }
-
-    // ---- coarsest: e = -(-L)^{-1} r in FP64.  16 threads per row of the
-    // inverse, each summing every 16th entry (loads unrolled so that they are
-    // in flight together), then a 16-lane shuffle reduction.
-    {
-        const int l = nl - 1;
-        const LGeo<T>& G = L[l];
-        T *ex = F(l, 0), *ey = F(l, 1), *rx = F(l, 2), *ry = F(l, 3);
-        const int nvx = G.ny * (G.nx - 1);
-        const int n = A.nc;
-        for (int m = tid; m < n; m += nthr) {
-            int i, j;
-            if (m < nvx) { i = 1 + m / (G.nx - 1); j = 1 + m % (G.nx - 1); rs[m] = (double)rx[i * G.P + j]; }
-            else { const int mm = m - nvx; i = 1 + mm / G.nx; j = 1 + mm % G.nx; rs[m] = (double)ry[i * G.P + j]; }
-        }
-        __syncthreads();
-        auto put = [&](int m, double sv) {
-            const T e = (T)(-sv);
-            if (m < nvx) {
-                const int i = 1 + m / (G.nx - 1), j = 1 + m % (G.nx - 1);
-                const int c = i * G.P + j;
-                ex[c] = e;
-                if (i == 1) ex[c - G.P] = K[l].mirS * e;
-                if (i == G.ny) ex[c + G.P] = K[l].mirN * e;
-            } else {
-                const int mm = m - nvx;
-                const int i = 1 + mm / G.nx, j = 1 + mm % G.nx;
-                const int c = i * G.P + j;
-                ey[c] = e;
-                if (j == 1) ey[c - 1] = K[l].mirW * e;
-                if (j == G.nx) ey[c + 1] = K[l].mirE * e;
-            }
-        };
-        if (minv_regs) {
-#pragma unroll
-            for (int r = 0; r < RM; ++r) {
-                const int m = grp + r * ngrp;
-                double sv = 0.0;
-#pragma unroll
-                for (int k = 0; k < KM; ++k) {
-                    const int q = sub + 16 * k;
-                    if (q < n) sv += mv[r][k] * rs[q];
-                }
-                for (int o = 8; o > 0; o >>= 1) sv += __shfl_xor(sv, o, 16);
-                if (sub == 0 && m < n) put(m, sv);
-            }
-        }
-        // otherwise two rows per 16-lane group at a time, column loop unrolled:
-        // the loads of both rows are in flight together
-        for (int m0 = minv_regs ? n : grp; m0 < n; m0 += 2 * ngrp) {
-            const int m1 = m0 + ngrp;
-            const double* row0 = A.Minv + (size_t)m0 * n;
-            const double* row1 = A.Minv + (size_t)(m1 < n ? m1 : m0) * n;
-            double s0 = 0.0, s1 = 0.0;
-#pragma unroll 8
-            for (int q = sub; q < n; q += 16) {
-                const double x = rs[q];
-                s0 += row0[q] * x;
-                s1 += row1[q] * x;
-            }
-            for (int o = 8; o > 0; o >>= 1) {
-                s0 += __shfl_xor(s0, o, 16);
-                s1 += __shfl_xor(s1, o, 16);
-            }
-            if (sub == 0) {
-                put(m0, s0);
-                if (m1 < n) put(m1, s1);
-            }
-        }
-        __syncthreads();
-    }
-
-    // ---- up: prolong + correct, post-smooth
-    for (int l = nl - 2; l >= 0; --l) {
-        const LGeo<T> G = L[l];
-        const LGeo<T> C = L[l + 1];
-        const LevelC<T> Kl = K[l];
-        T *ex = F(l, 0), *ey = F(l, 1);
-        const T *ecx = F(l + 1, 0), *ecy = F(l + 1, 1);
-        int rt, rs_, ct, cs_;
-        rowmap(G.nx, rt, rs_, ct, cs_);
-        for (int i = 1 + rt; i <= G.ny; i += rs_) {
-            for (int j = 1 + ct; j <= G.nx; j += cs_) {
-                const int c = i * G.P + j;
-                if (j < G.nx) {
-                    const T e = ex[c] + prolong_vx(ecx, C.P, i, j);
-                    ex[c] = e;
-                    if (i == 1) ex[c - G.P] = Kl.mirS * e;
-                    if (i == G.ny) ex[c + G.P] = Kl.mirN * e;
-                }
-                if (i < G.ny) {
-                    const T e = ey[c] + prolong_vy(ecy, C.P, i, j);
-                    ey[c] = e;
-                    if (j == 1) ey[c - 1] = Kl.mirW * e;
-                    if (j == G.nx) ey[c + 1] = Kl.mirE * e;
-                }
-            }
-        }
-        __syncthreads();
-        smooth(l, A.nu_post[l]);
-    }
-
-    // ---- write the top-level correction (every entry: walls zero, ghosts mirrored)
-    {
-        const int P = L[0].P;
-        const int Pg = A.g[0].pitch;
-        const T* sx = F(0, 0);
-        const T* sy = F(0, 1);
-        int rt, rs_, ct, cs_;
-        rowmap(P, rt, rs_, ct, cs_);
-        for (int i = rt; i < L[0].ny + 2; i += rs_) {
-            for (int j = ct; j < P; j += cs_) {
-                A.ex[i * Pg + j] = sx[i * P + j];
-                A.ey[i * Pg + j] = sy[i * P + j];
-            }
-        }
-    }
 }
 
 template <typename T>

@@ -197,13 +197,49 @@ hipError_t launch_p_sum(const Geom& g, const double* p, double* partial, int* nb
 hipError_t launch_p_shift(const Geom& g, double* p, const double* sum, hipStream_t st);
 
 // ------------------------------------------------------------------ fused.hip
+// One level of the coarse tail: sizes, LDS strides in bytes (row: one row of
+// nx + 2 word pairs; odd: from a row's start to its first odd column),
+// reciprocals of the divisors of its index arithmetic, and the constants of its
+// stencil (level_consts; idx_2 = 2 idx, idy_2 = 2 idy).
+template <typename T>
+struct TailLevel {
+    int nx, ny, pitch;
+    unsigned row, odd;
+    float rhp, rnx, rnx1, rp;        // 1 / (nx / 2), 1 / nx, 1 / (nx - 1), 1 / (nx + 2)
+    T idx, idy, idx2, idy2, idx_2, idy_2;
+    T mirW, mirE, mirS, mirN;
+};
+template <typename T>
+TailLevel<T> tail_level(const Geom& g) {
+    TailLevel<T> L{};
+    L.nx = g.nx;
+    L.ny = g.ny;
+    L.pitch = g.pitch;
+    L.row = (unsigned)(g.nx + 2) * 2 * sizeof(T);
+    L.odd = (unsigned)((g.nx + 3) / 2) * 2 * sizeof(T);
+    L.rhp = 1.0f / (float)(g.nx > 1 ? g.nx / 2 : 1);
+    L.rnx = 1.0f / (float)g.nx;
+    L.rnx1 = 1.0f / (float)(g.nx > 1 ? g.nx - 1 : 1);
+    L.rp = 1.0f / (float)(g.nx + 2);
+    L.idx = (T)(1.0 / g.dx);
+    L.idy = (T)(1.0 / g.dy);
+    L.idx2 = (T)(1.0 / (g.dx * g.dx));
+    L.idy2 = (T)(1.0 / (g.dy * g.dy));
+    L.idx_2 = (T)2 * L.idx;
+    L.idy_2 = (T)2 * L.idy;
+    L.mirW = (T)g.mir[0];
+    L.mirE = (T)g.mir[1];
+    L.mirS = (T)g.mir[2];
+    L.mirN = (T)g.mir[3];
+    return L;
+}
 template <typename T>
 struct CoarseArgs {
     int nl;                          // levels handled: 0 = top (read rx, ry; write ex, ey), nl-1 = coarsest
     int nc;                          // unknowns of the coarsest level (dense FP64 solve)
     int smoother;                    // TPH_SMOOTH_*
     T omega;
-    Geom g[kMaxLevels];
+    TailLevel<T> lv[kMaxLevels];
     const T* eb[kMaxLevels];
     const T* ep[kMaxLevels];
     int nu_pre[kMaxLevels];
@@ -214,8 +250,12 @@ struct CoarseArgs {
     T* ey;
     const double* Minv;
 };
+// LDS of the tail over levels g[0 .. nl-1] with nc coarsest unknowns
 template <typename T>
 size_t coarse_cycle_lds_bytes(const Geom* g, int nl, int nc);
+// threads per workgroup and cell pairs per thread of the tail with top level g
+struct TailShape { int threads, pairs; };
+TailShape coarse_cycle_shape(int nx, int ny);
 // mode: 0 plain sweep, 1 from a zero initial guess, 2 prolongation + correction then sweep
 enum TileMode { kTilePlain = 0, kTileZero = 1, kTileProlong = 2 };
 template <typename T>
@@ -227,7 +267,7 @@ template <typename T>
 hipError_t launch_res_restrict(const Geom& gf, const Geom& gc, const T* ex, const T* ey, const T* rx, const T* ry,
                                const T* eb, const T* ep, T* rcx, T* rcy, hipStream_t st);
 template <typename T>
-hipError_t launch_coarse_cycle(const CoarseArgs<T>& a, size_t lds_bytes, int max_lds, hipStream_t st);
+hipError_t launch_coarse_cycle(const CoarseArgs<T>& a, size_t lds_bytes, hipStream_t st);
 // Gauss-Seidel on LDS tiles, ns (1 or 2) full sweeps per pass; mode as
 // above; rr = 1 adds the residual and its restriction to the coarse level gc
 // (rcx, rcy); shape 0 / 1 selects the large / small tile.  The tile

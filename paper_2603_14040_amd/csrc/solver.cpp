@@ -509,7 +509,7 @@ tph_status vcycle_fused(tph_solver* s, int l, int* cur_out) {
         a.omega = om;
         for (int q = 0; q < a.nl; ++q) {
             const LevelBuf& Q = s->lev[l + q];
-            a.g[q] = Q.g;
+            a.lv[q] = tail_level<T>(Q.g);
             a.eb[q] = as<T>(Q.eb);
             a.ep[q] = as<T>(Q.ep);
             a.nu_pre[q] = Q.nu_pre;
@@ -520,7 +520,7 @@ tph_status vcycle_fused(tph_solver* s, int l, int* cur_out) {
         a.ex = as<T>(L.ex[0]);
         a.ey = as<T>(L.ey[0]);
         a.Minv = s->Minv;
-        TPH_HIP(launch_coarse_cycle<T>(a, s->lc_lds, s->max_lds, st));
+        TPH_HIP(launch_coarse_cycle<T>(a, s->lc_lds, st));
         *cur_out = 0;
         return TPH_OK;
     }
@@ -1469,36 +1469,38 @@ tph_status create_impl(const tph_desc* desc, void* stream, tph_solver* s) {
     s->lc = -1;
     // the coarse tail smooths with Jacobi or Gauss-Seidel only: the RAS smoothers run level by level
     if (desc->fused && nlev >= 2 && s->ncoarse <= 2048 && desc->coarse_level != -2 && !s->ras()) {
-        // a level qualifies when its tail fits in one workgroup's LDS (leaving
-        // room for the kernel's static tables) and its per-sweep work suits one
-        // workgroup (<= 64 x 64 cells); default: the finest such level
+        // A level qualifies when its per-sweep work suits one workgroup (<= 64 x
+        // 64 cells) and eight fields of it and six of each level below fit one
+        // workgroup's LDS (leaving room for the kernel's static tables); default:
+        // the finest such level.  The kernel itself needs less
+        // (coarse_cycle_lds_bytes).  Taking in a larger level does not pay: a
+        // 64 x 64 one makes the 1024^2 solve 15.6 ms instead of 13.8.
         const size_t budget = (size_t)std::min(s->max_lds, 160 * 1024) - 8 * 1024;
-        auto fits = [&](int l, size_t* need_out) {
+        const size_t w = s->mixed() ? sizeof(float) : sizeof(double);
+        auto eligible = [&](int l) {
+            size_t n = 2 * (size_t)(s->lev[l].g.ny + 2) * (s->lev[l].g.nx + 2);
+            for (int q = l; q < nlev; ++q) n += 6 * (size_t)(s->lev[q].g.ny + 2) * (s->lev[q].g.nx + 2);
+            return s->lev[l].g.nx * s->lev[l].g.ny <= 64 * 64 &&
+                   (n * w + 7) / 8 * 8 + (size_t)s->ncoarse * sizeof(double) <= budget;
+        };
+        auto need = [&](int l) {
             Geom gs[kMaxLevels];
             for (int q = l; q < nlev; ++q) gs[q - l] = s->lev[q].g;
-            const size_t need = s->mixed() ? coarse_cycle_lds_bytes<float>(gs, nlev - l, s->ncoarse)
-                                           : coarse_cycle_lds_bytes<double>(gs, nlev - l, s->ncoarse);
-            *need_out = need;
-            return s->lev[l].g.nx * s->lev[l].g.ny <= 64 * 64 && need <= budget;
+            return s->mixed() ? coarse_cycle_lds_bytes<float>(gs, nlev - l, s->ncoarse)
+                              : coarse_cycle_lds_bytes<double>(gs, nlev - l, s->ncoarse);
         };
-        size_t need = 0;
         if (desc->coarse_level >= 0) {
             const int l = desc->coarse_level;
-            if (l >= nlev - 1 || !fits(l, &need)) {
+            if (l >= nlev - 1 || !eligible(l)) {
                 set_error("coarse_level " + std::to_string(l) + " does not fit the single-workgroup coarse tail");
                 return TPH_ERR_INVALID;
             }
             s->lc = l;
-            s->lc_lds = need;
         } else {
-            for (int l = 0; l < nlev - 1; ++l) {
-                if (fits(l, &need)) {
-                    s->lc = l;
-                    s->lc_lds = need;
-                    break;
-                }
-            }
+            for (int l = 0; l < nlev - 1 && s->lc < 0; ++l)
+                if (eligible(l)) s->lc = l;
         }
+        if (s->lc >= 0) s->lc_lds = need(s->lc);
     }
     s->msw_mask = 0;
     s->shape_mask = 0;
