@@ -56,7 +56,7 @@ __global__ void k_coarse_assemble(Geom g, const double* __restrict__ eb, const d
     unknown_to_node(g, m, comp, i, j);
     const int P = g.pitch;
     const int c = i * P + j;
-    const double idx2 = 1.0 / (g.dx * g.dx), idy2 = 1.0 / (g.dy * g.dy), idxy = 1.0 / (g.dx * g.dy);
+    const double idx2 = g.idx2, idy2 = g.idy2, idxy = 1.0 / (g.dx * g.dy);
     if (comp == 0) {
         const double er = ep[c + 1], el = ep[c], bt = eb[c], bb = eb[c - P];
         add_ref(g, row, 0, i, j + 1, 2 * er * idx2);

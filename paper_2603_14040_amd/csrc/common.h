@@ -22,9 +22,18 @@ struct Geom {
     int nx, ny;          // cells
     int pitch;           // elements per row
     double dx, dy;
+    double idx, idy, idx2, idy2;   // 1 / dx, 1 / dy, 1 / dx^2, 1 / dy^2 (set_spacing): formed
+                                   // on the host, four FP64 divisions less in every thread
     float mir[4];        // ghost = mir * interior at walls W, E, S, N (+1 free slip, -1 no slip)
     __host__ __device__ size_t elems() const { return (size_t)(ny + 2) * pitch; }
-    __host__ __device__ size_t idx(int i, int j) const { return (size_t)i * pitch + j; }
+    void set_spacing(double hx, double hy) {
+        dx = hx;
+        dy = hy;
+        idx = 1.0 / dx;
+        idy = 1.0 / dy;
+        idx2 = 1.0 / (dx * dx);
+        idy2 = 1.0 / (dy * dy);
+    }
 };
 
 inline int pitch_for(int nx) { return ((nx + 2 + kAlign - 1) / kAlign) * kAlign; }

@@ -12,7 +12,7 @@ namespace {
 using namespace dev;
 
 template <typename T, int TW, int TH, int SM, int MODE>
-__global__ __launch_bounds__(kTileThreads) void k_smooth_tile(Geom g, Geom gc, const T* __restrict__ exi,
+__global__ __launch_bounds__(kTileThreads, kTileWaves) void k_smooth_tile(Geom g, Geom gc, const T* __restrict__ exi,
                                                     const T* __restrict__ eyi, T* __restrict__ exo,
                                                     T* __restrict__ eyo, const T* __restrict__ rx,
                                                     const T* __restrict__ ry, const T* __restrict__ eb,

@@ -27,27 +27,37 @@ namespace tph {
 namespace dev {
 
 
+// a * b + c with one rounding, where which product of a sum of two goes inside
+// must not depend on the code around it
+__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
 enum { kModePlain = kTilePlain, kModeZero = kTileZero, kModeProlong = kTileProlong };
 enum { kSmJacobi = 0, kSmGS = 1 };
 
-// bilinear prolongation of the coarse vx / vy correction to fine node (i, j)
-// (same weights as k_prolong_add; coarse ghosts hold mirrored values)
+// Bilinear prolongation of the coarse vx / vy correction to fine node (i, j)
+// (same weights as k_prolong_add; coarse ghosts hold mirrored values).  A node on
+// a coarse column (row) reads it twice with half the weight, which is exact:
+// neighbouring lanes then take one path (2048^2 sweep with prolongation 43 -> 40
+// us from this alone).
 template <typename T>
 __device__ __forceinline__ T prolong_vx(const T* __restrict__ ec, int Pc, int i, int j) {
     const int I0 = (i + 1) >> 1;
     const int I1 = (i & 1) ? I0 - 1 : I0 + 1;
-    const int J = j >> 1;
-    if ((j & 1) == 0) return (T)0.75 * ec[I0 * Pc + J] + (T)0.25 * ec[I1 * Pc + J];
-    return (T)0.375 * (ec[I0 * Pc + J] + ec[I0 * Pc + J + 1]) + (T)0.125 * (ec[I1 * Pc + J] + ec[I1 * Pc + J + 1]);
+    const int J = j >> 1, e = j & 1;
+    const T* a = ec + (I0 * Pc + J);
+    const T* b = ec + (I1 * Pc + J);
+    return (T)0.375 * (a[0] + a[e]) + (T)0.125 * (b[0] + b[e]);
 }
 
 template <typename T>
 __device__ __forceinline__ T prolong_vy(const T* __restrict__ ec, int Pc, int i, int j) {
     const int J0 = (j + 1) >> 1;
     const int J1 = (j & 1) ? J0 - 1 : J0 + 1;
-    const int I = i >> 1;
-    if ((i & 1) == 0) return (T)0.75 * ec[I * Pc + J0] + (T)0.25 * ec[I * Pc + J1];
-    return (T)0.375 * (ec[I * Pc + J0] + ec[(I + 1) * Pc + J0]) + (T)0.125 * (ec[I * Pc + J1] + ec[(I + 1) * Pc + J1]);
+    const int I = i >> 1, e = (i & 1) ? Pc : 0;
+    const T* a = ec + (I * Pc + J0);
+    const T* b = ec + (I * Pc + J1);
+    return (T)0.375 * (a[0] + a[e]) + (T)0.125 * (b[0] + b[e]);
 }
 
 __device__ __forceinline__ bool is_vx(const Geom& g, int i, int j) { return i >= 1 && i <= g.ny && j >= 1 && j < g.nx; }
@@ -100,36 +110,71 @@ constexpr int prolong_rows() { return RH / 2 + 4; }
 // slower again), with bitwise the same results, since nodes of one stage
 // are independent of each other.
 constexpr int kTileThreads = 512;
+// Waves per SIMD the one-sweep tile kernels are compiled for: 8, i.e. at most
+// 64 registers, so that four workgroups share a CU and the 1024 tiles of a
+// 1024^2 level run in one round (the sweep with prolongation took 66 by itself,
+// three per CU and a second, nearly empty round: 16.6 us, now 16.3 from this
+// alone).
+constexpr int kTileWaves = 8;
 
 template <int N>
 constexpr int tile_iters() { return (N + kTileThreads - 1) / kTileThreads; }
 
-// load the iterate (zero / from memory / from memory + prolongated coarse
-// correction) and the viscosities of the region starting at (gi0, gj0)
-template <typename T, int RW, int RH, int MODE, bool IN>
+// Entries of a field at byte offsets from a tile's first entry: the pointer is
+// uniform and the offset a non-negative 32-bit value, so a load takes no
+// address arithmetic of its own and the offset serves every field.
+template <typename V, typename T>
+__device__ __forceinline__ V tile_ld(const T* __restrict__ p, unsigned off) {
+    return *(const V*)((const char*)p + off);
+}
+template <typename T>
+__device__ __forceinline__ void tile_st(T* __restrict__ p, unsigned off, T v) {
+    *(T*)((char*)p + off) = v;
+}
+template <typename T> struct TilePair;
+template <> struct TilePair<float> { typedef float type __attribute__((ext_vector_type(2))); };
+template <> struct TilePair<double> { typedef double type __attribute__((ext_vector_type(2))); };
+
+// Load the iterate (zero / from memory / from memory + prolongated coarse
+// correction) and the viscosities of the region starting at (gi0, gj0).  gj0 is
+// odd and columns 1, 65, .. start a segment, so two neighbouring columns are
+// one aligned vector: a thread takes pairs, which halves the loads, LDS stores
+// and index arithmetic of the phase and lets the two nodes of a pair share the
+// coarse values they interpolate.  These passes are bound by the instructions
+// they issue (some 350 vector instructions per wave in a sweep from zero, 480
+// with prolongation, over 600 before): the FP32 sweep with prolongation takes
+// 15.0 us on 1024^2 (17.5) and 35 on 2048^2 (43).
+template <typename T, int RW, int RH, int H, int MODE, bool IN>
 __device__ __forceinline__ void tile_load(const Geom& g, const Geom& gc, int gi0, int gj0, const T* __restrict__ exi,
                                           const T* __restrict__ eyi, const T* __restrict__ eb,
                                           const T* __restrict__ ep, const T* __restrict__ ecx,
                                           const T* __restrict__ ecy, T* sx, T* sy, T* sb, T* sp, T* scx, T* scy,
                                           const LevelC<T>& k) {
-    constexpr int RN = RW * RH, IT = tile_iters<RN>();
+    using V2 = typename TilePair<T>::type;
+    constexpr int HW = RW / 2, RN = HW * RH, IT = tile_iters<RN>();
     constexpr int CR = prolong_rows<RH>(), CC = prolong_rows<RW>(), ITC = tile_iters<CR * CC>();
     constexpr bool kIter = MODE != kModeZero;
     const int tid = threadIdx.x;
     const int P = g.pitch;
-    T vb[IT], vp[IT], vx[kIter ? IT : 1], vy[kIter ? IT : 1];
+    const ptrdiff_t base = (ptrdiff_t)gi0 * P + gj0;
+    const T *pb = eb + base, *pp = ep + base, *px = kIter ? exi + base : nullptr, *py = kIter ? eyi + base : nullptr;
+    const V2 zero = {(T)0, (T)0};
+    V2 vb[IT], vp[IT], vx[kIter ? IT : 1], vy[kIter ? IT : 1];
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
         const int q = tid + it * kTileThreads;
-        const int a = q / RW, b = q - (q / RW) * RW;
-        const int gi = gi0 + a, gj = gj0 + b;
-        const bool in = q < RN && (IN || (gi >= 0 && gi <= g.ny + 1 && gj >= 0 && gj <= g.nx + 1));
-        const int c = in ? gi * P + gj : 0;
-        vb[it] = in ? eb[c] : (T)0;
-        vp[it] = in ? ep[c] : (T)0;
+        const int a = q / HW, m = q - (q / HW) * HW;
+        const int gi = gi0 + a, gj = gj0 + 2 * m;
+        // columns 0 .. nx + 1 hold entries; the pairs (-1, 0) and (nx + 1, nx + 2) hold one each (their
+        // other half is padding, zero here)
+        const bool in = q < RN && (IN || (gi >= 0 && gi <= g.ny + 1 && gj >= -1 && gj <= g.nx + 1));
+        // (lanes without a pair repeat the tile's first own one)
+        const unsigned off = (unsigned)(in ? a * P + 2 * m : H * P + H) * (unsigned)sizeof(T);
+        vb[it] = tile_ld<V2>(pb, off);
+        vp[it] = tile_ld<V2>(pp, off);
         if (kIter) {
-            vx[it] = in ? exi[c] : (T)0;
-            vy[it] = in ? eyi[c] : (T)0;
+            vx[it] = tile_ld<V2>(px, off);
+            vy[it] = tile_ld<V2>(py, off);
         }
     }
     // first coarse row / column of the prolongation window: floor(gi0 / 2) - 1
@@ -137,6 +182,8 @@ __device__ __forceinline__ void tile_load(const Geom& g, const Geom& gc, int gi0
     const int ci0 = ((gi0 + 64) >> 1) - 32 - 1;
     const int cj0 = ((gj0 + 64) >> 1) - 32 - 1;
     if (MODE == kModeProlong) {
+        const int Pc = gc.pitch;
+        const T *qx = ecx + ((ptrdiff_t)ci0 * Pc + cj0), *qy = ecy + ((ptrdiff_t)ci0 * Pc + cj0);
         T wx[ITC], wy[ITC];
 #pragma unroll
         for (int it = 0; it < ITC; ++it) {
@@ -144,9 +191,12 @@ __device__ __forceinline__ void tile_load(const Geom& g, const Geom& gc, int gi0
             const int a = q / CC, b = q - (q / CC) * CC;
             const int I = ci0 + a, J = cj0 + b;
             const bool in = q < CR * CC && I >= 0 && I <= gc.ny + 1 && J >= 0 && J <= gc.nx + 1;
-            const int c = in ? I * gc.pitch + J : 0;
-            wx[it] = in ? ecx[c] : (T)0;
-            wy[it] = in ? ecy[c] : (T)0;
+            wx[it] = wy[it] = (T)0;
+            if (in) {
+                const unsigned off = (unsigned)(a * Pc + b) * (unsigned)sizeof(T);
+                wx[it] = tile_ld<T>(qx, off);
+                wy[it] = tile_ld<T>(qy, off);
+            }
         }
 #pragma unroll
         for (int it = 0; it < ITC; ++it) {
@@ -162,31 +212,58 @@ __device__ __forceinline__ void tile_load(const Geom& g, const Geom& gc, int gi0
     for (int it = 0; it < IT; ++it) {
         const int q = tid + it * kTileThreads;
         if (q >= RN) continue;
-        sb[q] = vb[it];
-        sp[q] = vp[it];
-        if (MODE == kModeZero) {
-            sx[q] = (T)0;
-            sy[q] = (T)0;
-        } else {
-            T ux = vx[it], uy = vy[it];
-            if (MODE == kModeProlong) {
-                // coarse indices are taken relative to the LDS window
-                const int a = q / RW, b = q - (q / RW) * RW;
-                const int gi = gi0 + a, gj = gj0 + b;
-                if (ux_at<IN>(g, gi, gj)) ux += prolong_vx(scx - ci0 * CC - cj0, CC, gi, gj);
-                if (uy_at<IN>(g, gi, gj)) uy += prolong_vy(scy - ci0 * CC - cj0, CC, gi, gj);
+        const int a = q / HW, m = q - (q / HW) * HW;
+        if (!IN) {
+            const int gi = gi0 + a, gj = gj0 + 2 * m;
+            const bool row = gi >= 0 && gi <= g.ny + 1;
+            const bool lo = row && gj >= 0 && gj <= g.nx + 1, hi = row && gj >= -1 && gj <= g.nx;
+            vb[it] = V2{lo ? vb[it].x : (T)0, hi ? vb[it].y : (T)0};
+            vp[it] = V2{lo ? vp[it].x : (T)0, hi ? vp[it].y : (T)0};
+            if (kIter) {
+                vx[it] = V2{lo ? vx[it].x : (T)0, hi ? vx[it].y : (T)0};
+                vy[it] = V2{lo ? vy[it].x : (T)0, hi ? vy[it].y : (T)0};
             }
-            sx[q] = ux;
-            sy[q] = uy;
+        }
+        ((V2*)sb)[q] = vb[it];
+        ((V2*)sp)[q] = vp[it];
+        if (MODE == kModeZero) {
+            ((V2*)sx)[q] = zero;
+            ((V2*)sy)[q] = zero;
+        } else {
+            V2 ux = vx[it], uy = vy[it];
+            if (MODE == kModeProlong) {
+                // bilinear, the weights and order of prolong_vx / prolong_vy; coarse
+                // rows and columns relative to the LDS window.  Columns gj = 2M + 1 (between
+                // coarse lines M, M + 1 for vx) and gj + 1 (on line M + 1).
+                const int gi = gi0 + a, gj = gj0 + 2 * m;
+                const int M = ((gj + 63) >> 1) - 32;                                // (gj - 1) / 2
+                const int odd = gi & 1, I0 = (gi + 1) >> 1, I1 = odd ? I0 - 1 : I0 + 1, I = gi >> 1;
+                const T* x0 = scx + ((I0 - ci0) * CC + (M - cj0));
+                const T* x1 = scx + ((I1 - ci0) * CC + (M - cj0));
+                const T n0 = x0[0], n1 = x0[1], f0 = x1[0], f1 = x1[1];
+                const T* y0 = scy + ((I - ci0) * CC + (M - cj0));
+                const T* y1 = y0 + (odd ? CC : 0);
+                const T w = y0[0] + y1[0], c = y0[1] + y1[1], e = y0[2] + y1[2];    // columns M, M + 1, M + 2
+                const T px0 = fma_((T)0.375, n0 + n1, (T)0.125 * (f0 + f1));
+                const T px1 = fma_((T)0.75, n1, (T)0.25 * f1);
+                const T py0 = fma_((T)0.375, c, (T)0.125 * w), py1 = fma_((T)0.375, c, (T)0.125 * e);
+                if (ux_at<IN>(g, gi, gj)) ux.x += px0;
+                if (ux_at<IN>(g, gi, gj + 1)) ux.y += px1;
+                if (uy_at<IN>(g, gi, gj)) uy.x += py0;
+                if (uy_at<IN>(g, gi, gj + 1)) uy.y += py1;
+            }
+            ((V2*)sx)[q] = ux;
+            ((V2*)sy)[q] = uy;
         }
     }
     __syncthreads();
     if (MODE == kModeProlong && !IN) {
         // ghosts mirror the corrected interior values
+        constexpr int RN1 = RW * RH, IT1 = tile_iters<RN1>();
 #pragma unroll
-        for (int it = 0; it < IT; ++it) {
+        for (int it = 0; it < IT1; ++it) {
             const int q = tid + it * kTileThreads;
-            if (q >= RN) continue;
+            if (q >= RN1) continue;
             const int a = q / RW, b = q - (q / RW) * RW;
             const int gi = gi0 + a, gj = gj0 + b;
             if (gj >= 1 && gj < g.nx) {
@@ -238,6 +315,7 @@ __device__ __forceinline__ void stage_rhs(const Geom& g, int gi0, int gj0, const
     using S = Stages<TW, TH, H, NSTAGE>;
     const int tid = threadIdx.x;
     const int P = g.pitch;
+    const T *px = rx + ((ptrdiff_t)gi0 * P + gj0), *py = ry + ((ptrdiff_t)gi0 * P + gj0);
 #pragma unroll
     for (int s = 0; s < NSTAGE; ++s) {
         const int comp = (s >> 1) & 1;
@@ -248,8 +326,8 @@ __device__ __forceinline__ void stage_rhs(const Geom& g, int gi0, int gj0, const
             stage_node<TW, TH, H>(s, q, gi0, gj0, a, b);
             const int gi = gi0 + a, gj = gj0 + b;
             const bool ok = q < S::rows(s) * S::half(s) && (comp == 0 ? ux_at<IN>(g, gi, gj) : uy_at<IN>(g, gi, gj));
-            const int c = ok ? gi * P + gj : 0;
-            rr[S::offset(s) + it] = ok ? (comp == 0 ? rx[c] : ry[c]) : (T)0;
+            rr[S::offset(s) + it] = (T)0;
+            if (ok) rr[S::offset(s) + it] = tile_ld<T>(comp == 0 ? px : py, (unsigned)(a * P + b) * (unsigned)sizeof(T));
         }
     }
 }
@@ -316,7 +394,9 @@ template <typename T, int TW, int TH, int H, bool IN>
 __device__ __forceinline__ void tile_store(const Geom& g, int gi0, int gj0, const T* sx, const T* sy,
                                            T* __restrict__ exo, T* __restrict__ eyo, const LevelC<T>& k) {
     constexpr int RW = TW + 2 * H;
+    constexpr unsigned Z = sizeof(T);
     const int P = g.pitch;
+    T *px = exo + ((ptrdiff_t)gi0 * P + gj0), *py = eyo + ((ptrdiff_t)gi0 * P + gj0);
 #pragma unroll
     for (int it = 0; it < tile_iters<TW * TH>(); ++it) {
         const int q = threadIdx.x + it * kTileThreads;
@@ -324,18 +404,18 @@ __device__ __forceinline__ void tile_store(const Geom& g, int gi0, int gj0, cons
         const int a = H + q / TW, b = H + (q - (q / TW) * TW);
         const int gi = gi0 + a, gj = gj0 + b;
         const int c = a * RW + b;
-        const int cg = gi * P + gj;
+        const unsigned off = (unsigned)(a * P + b) * Z;
         if (ux_at<IN>(g, gi, gj)) {
             const T e = sx[c];
-            exo[cg] = e;
-            if (!IN && gi == 1) exo[cg - P] = k.mirS * e;
-            if (!IN && gi == g.ny) exo[cg + P] = k.mirN * e;
+            tile_st(px, off, e);
+            if (!IN && gi == 1) tile_st(px, off - P * Z, k.mirS * e);
+            if (!IN && gi == g.ny) tile_st(px, off + P * Z, k.mirN * e);
         }
         if (uy_at<IN>(g, gi, gj)) {
             const T e = sy[c];
-            eyo[cg] = e;
-            if (!IN && gj == 1) eyo[cg - 1] = k.mirW * e;
-            if (!IN && gj == g.nx) eyo[cg + 1] = k.mirE * e;
+            tile_st(py, off, e);
+            if (!IN && gj == 1) tile_st(py, off - Z, k.mirW * e);
+            if (!IN && gj == g.nx) tile_st(py, off + Z, k.mirE * e);
         }
     }
 }
@@ -411,11 +491,14 @@ __device__ __forceinline__ void gs_tile_run(const Geom& g, const Geom& gc, const
             const int a = q / TRW, b = q - (q / TRW) * TRW;
             const int gi = i0 - 1 + a, gj = j0 - 1 + b;
             const bool okx = q < TRW * TRH && ux_at<IN>(g, gi, gj), oky = q < TRW * TRH && uy_at<IN>(g, gi, gj);
-            rrx[it] = okx ? rx[gi * P + gj] : (T)0;
-            rry[it] = oky ? ry[gi * P + gj] : (T)0;
+            const unsigned off = (unsigned)(a * P + b) * (unsigned)sizeof(T);
+            const ptrdiff_t base = (ptrdiff_t)(i0 - 1) * P + (j0 - 1);
+            rrx[it] = rry[it] = (T)0;
+            if (okx) rrx[it] = tile_ld<T>(rx + base, off);
+            if (oky) rry[it] = tile_ld<T>(ry + base, off);
         }
     }
-    tile_load<T, RW, RH, MODE, IN>(g, gc, gi0, gj0, exi, eyi, eb, ep, ecx, ecy, sx, sy, sb, sp, scx, scy, k);
+    tile_load<T, RW, RH, H, MODE, IN>(g, gc, gi0, gj0, exi, eyi, eb, ep, ecx, ecy, sx, sy, sb, sp, scx, scy, k);
     gs_stages<T, TW, TH, H, 4 * NS, IN, (NS > 1 || RR), MODE == kModeZero>(g, gi0, gj0, sx, sy, sb, sp, rr, omega,
                                                                           k);
     tile_store<T, TW, TH, H, IN>(g, gi0, gj0, sx, sy, exo, eyo, k);
@@ -457,7 +540,7 @@ __device__ __forceinline__ void gs_tile_body(const Geom& g, const Geom& gc, cons
     constexpr int CN = MODE == kModeProlong ? prolong_rows<RH>() * prolong_rows<RW>() : 1;
     constexpr int TRW = RR ? TW + 2 : 1, TRH = RR ? TH + 2 : 1;
     static_assert((4 * RN + 2 * CN + 2 * TRW * TRH) * sizeof(T) <= 65536, "tile exceeds 64 KB of LDS");
-    __shared__ T sx[RN], sy[RN], sb[RN], sp[RN];
+    __shared__ __align__(16) T sx[RN], sy[RN], sb[RN], sp[RN];
     __shared__ T scx[CN], scy[CN];
     __shared__ T stx[TRW * TRH], sty[TRW * TRH];
     // uniform per tile: interior tiles take the check-free path
@@ -469,7 +552,8 @@ __device__ __forceinline__ void gs_tile_body(const Geom& g, const Geom& gc, cons
                                                     omega, tbx, tby, sx, sy, sb, sp, scx, scy, stx, sty);
 }
 
-// one damped Jacobi sweep on an LDS tile (halo 1)
+// one damped Jacobi sweep on an LDS tile (halo 2: one node would do, an even
+// halo keeps the region's columns in aligned pairs)
 template <typename T, int TW, int TH, int MODE>
 __device__ __forceinline__ void jacobi_tile_body(const Geom& g, const Geom& gc, const T* __restrict__ exi,
                                                  const T* __restrict__ eyi, T* __restrict__ exo,
@@ -477,10 +561,10 @@ __device__ __forceinline__ void jacobi_tile_body(const Geom& g, const Geom& gc, 
                                                  const T* __restrict__ ry, const T* __restrict__ eb,
                                                  const T* __restrict__ ep, const T* __restrict__ ecx,
                                                  const T* __restrict__ ecy, T omega, int tbx, int tby) {
-    constexpr int H = 1;
+    constexpr int H = 2;
     constexpr int RW = TW + 2 * H, RH = TH + 2 * H, RN = RW * RH;
     constexpr int CN = MODE == kModeProlong ? prolong_rows<RH>() * prolong_rows<RW>() : 1;
-    __shared__ T sx[RN], sy[RN], sb[RN], sp[RN];
+    __shared__ __align__(16) T sx[RN], sy[RN], sb[RN], sp[RN];
     __shared__ T scx[CN], scy[CN];
     constexpr int IT = tile_iters<TW * TH>();
     const int i0 = 1 + tby * TH, j0 = 1 + tbx * TW;
@@ -496,7 +580,7 @@ __device__ __forceinline__ void jacobi_tile_body(const Geom& g, const Geom& gc, 
         rrx[it] = q < TW * TH && is_vx(g, gi, gj) ? rx[gi * P + gj] : (T)0;
         rry[it] = q < TW * TH && is_vy(g, gi, gj) ? ry[gi * P + gj] : (T)0;
     }
-    tile_load<T, RW, RH, MODE, false>(g, gc, gi0, gj0, exi, eyi, eb, ep, ecx, ecy, sx, sy, sb, sp, scx, scy, k);
+    tile_load<T, RW, RH, H, MODE, false>(g, gc, gi0, gj0, exi, eyi, eb, ep, ecx, ecy, sx, sy, sb, sp, scx, scy, k);
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
         const int q = threadIdx.x + it * kTileThreads;
@@ -560,13 +644,17 @@ __device__ __forceinline__ void res_restrict_body(const Geom& g, const Geom& gc,
     constexpr int ITL = (LN + NT - 1) / NT, ITR = (RN + NT - 1) / NT;
     // every load of the tile in flight before the first use (see kTileThreads)
     T vx[ITL], vy[ITL], vb[ITL], vp[ITL], rrx[ITR], rry[ITR];
+    const ptrdiff_t rbase = (ptrdiff_t)fi0 * P + fj0, lbase = (ptrdiff_t)li0 * P + lj0;
+    const T *prx = rx + rbase, *pry = ry + rbase, *px = ex + lbase, *py = ey + lbase, *pb = eb + lbase, *pp = ep + lbase;
 #pragma unroll
     for (int it = 0; it < ITR; ++it) {
         const int q = tid + it * NT;
         const int a = q / RC, b = q - (q / RC) * RC;
         const int gi = fi0 + a, gj = fj0 + b;
-        rrx[it] = q < RN && is_vx(g, gi, gj) ? rx[gi * P + gj] : (T)0;
-        rry[it] = q < RN && is_vy(g, gi, gj) ? ry[gi * P + gj] : (T)0;
+        const unsigned off = (unsigned)(a * P + b) * (unsigned)sizeof(T);
+        rrx[it] = rry[it] = (T)0;
+        if (q < RN && is_vx(g, gi, gj)) rrx[it] = tile_ld<T>(prx, off);
+        if (q < RN && is_vy(g, gi, gj)) rry[it] = tile_ld<T>(pry, off);
     }
 #pragma unroll
     for (int it = 0; it < ITL; ++it) {
@@ -574,11 +662,14 @@ __device__ __forceinline__ void res_restrict_body(const Geom& g, const Geom& gc,
         const int a = q / LC, b = q - (q / LC) * LC;
         const int gi = li0 + a, gj = lj0 + b;
         const bool in = q < LN && gi >= 0 && gi <= g.ny + 1 && gj >= 0 && gj <= g.nx + 1;
-        const int c = in ? gi * P + gj : 0;
-        vx[it] = in ? ex[c] : (T)0;
-        vy[it] = in ? ey[c] : (T)0;
-        vb[it] = in ? eb[c] : (T)0;
-        vp[it] = in ? ep[c] : (T)0;
+        const unsigned off = (unsigned)(a * P + b) * (unsigned)sizeof(T);
+        vx[it] = vy[it] = vb[it] = vp[it] = (T)0;
+        if (in) {
+            vx[it] = tile_ld<T>(px, off);
+            vy[it] = tile_ld<T>(py, off);
+            vb[it] = tile_ld<T>(pb, off);
+            vp[it] = tile_ld<T>(pp, off);
+        }
     }
 #pragma unroll
     for (int it = 0; it < ITL; ++it) {

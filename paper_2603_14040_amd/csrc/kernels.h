@@ -221,10 +221,10 @@ TailLevel<T> tail_level(const Geom& g) {
     L.rnx = 1.0f / (float)g.nx;
     L.rnx1 = 1.0f / (float)(g.nx > 1 ? g.nx - 1 : 1);
     L.rp = 1.0f / (float)(g.nx + 2);
-    L.idx = (T)(1.0 / g.dx);
-    L.idy = (T)(1.0 / g.dy);
-    L.idx2 = (T)(1.0 / (g.dx * g.dx));
-    L.idy2 = (T)(1.0 / (g.dy * g.dy));
+    L.idx = (T)g.idx;
+    L.idy = (T)g.idy;
+    L.idx2 = (T)g.idx2;
+    L.idy2 = (T)g.idy2;
     L.idx_2 = (T)2 * L.idx;
     L.idy_2 = (T)2 * L.idy;
     L.mirW = (T)g.mir[0];

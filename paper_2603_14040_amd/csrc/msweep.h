@@ -24,7 +24,7 @@ struct TileShape {
 };
 
 template <typename T, int TW, int TH, int NS, int MODE, int RR>
-__global__ __launch_bounds__(kTileThreads) void k_gs_tile(Geom g, Geom gc, const T* __restrict__ exi,
+__global__ __launch_bounds__(kTileThreads, NS == 1 ? kTileWaves : 1) void k_gs_tile(Geom g, Geom gc, const T* __restrict__ exi,
                                                          const T* __restrict__ eyi, T* __restrict__ exo,
                                                          T* __restrict__ eyo, const T* __restrict__ rx,
                                                          const T* __restrict__ ry, const T* __restrict__ eb,

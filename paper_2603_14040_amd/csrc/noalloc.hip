@@ -221,8 +221,7 @@ extern "C" tph_status tph_energy_residual_noalloc(const tph_desc* desc, const do
     g.nx = desc->nx;
     g.ny = desc->ny;
     g.pitch = q.pitch;
-    g.dx = desc->lx / desc->nx;
-    g.dy = desc->ly / desc->ny;
+    g.set_spacing(desc->lx / desc->nx, desc->ly / desc->ny);
     for (int w = 0; w < 4; ++w) g.mir[w] = desc->bc[w] == TPH_NO_SLIP ? -1.0f : 1.0f;
     q.k = level_consts<double>(g);
     q.idx = q.k.idx;

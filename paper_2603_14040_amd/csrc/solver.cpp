@@ -1425,8 +1425,7 @@ tph_status create_impl(const tph_desc* desc, void* stream, tph_solver* s) {
             g.ny = desc->ny >> l;
         }
         g.pitch = pitch_for(g.nx);
-        g.dx = desc->lx / g.nx;
-        g.dy = desc->ly / g.ny;
+        g.set_spacing(desc->lx / g.nx, desc->ly / g.ny);
         for (int w = 0; w < 4; ++w) g.mir[w] = desc->bc[w] == TPH_FREE_SLIP ? 1.0f : -1.0f;
         s->lev[l].nu_pre = level_sweeps(desc->nu_pre, desc->nu_growth, l);
         s->lev[l].nu_post = level_sweeps(desc->nu_post, desc->nu_growth, l);

@@ -21,10 +21,10 @@ struct LevelC {             // level constants in the arithmetic type
 template <typename T>
 __host__ __device__ inline LevelC<T> level_consts(const Geom& g) {
     LevelC<T> k;
-    k.idx = (T)(1.0 / g.dx);
-    k.idy = (T)(1.0 / g.dy);
-    k.idx2 = (T)(1.0 / (g.dx * g.dx));
-    k.idy2 = (T)(1.0 / (g.dy * g.dy));
+    k.idx = (T)g.idx;
+    k.idy = (T)g.idy;
+    k.idx2 = (T)g.idx2;
+    k.idy2 = (T)g.idy2;
     k.mirW = (T)g.mir[0];
     k.mirE = (T)g.mir[1];
     k.mirS = (T)g.mir[2];
