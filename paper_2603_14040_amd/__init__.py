@@ -278,7 +278,7 @@ class Solver:
         return vx, vy, p, self._info(info, st, [])
 
     def apply(self, vx, vy, p):
-        ax, ay, ap = self.zeros(), self.zeros(), self.zeros()
+        ax, ay, ap = [torch.empty(self.shape, dtype=torch.float64, device=self.device) for _ in range(3)]
         self._sync_in()
         _lib.check("tph_apply", self._lib.tph_apply(self._h, self._p(vx, "vx"), self._p(vy, "vy"), self._p(p, "p"),
                                                     self._p(ax, "ax"), self._p(ay, "ay"), self._p(ap, "ap")))

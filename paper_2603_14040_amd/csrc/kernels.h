@@ -14,6 +14,11 @@ enum class ResMode { kResidual = 0, kApply = 1 };
 hipError_t launch_outer_residual(const Geom& g, Vec3 x, const Vec3* b, const double* eb, const double* ep,
                                  Vec3 out, ResMode mode, bool energy, double* partial, int* nblk_out,
                                  hipStream_t st, bool b_scaled = false);
+// (ax, ay, ap) = A (vx, vy, p) between the caller's dense (ny + 2) x (nx + 2)
+// arrays, every entry of the outputs written (zero outside the equation rows);
+// the outputs must not overlap the inputs or each other
+hipError_t launch_apply_dense(const Geom& g, const double* vx, const double* vy, const double* p, const double* eb,
+                              const double* ep, double* ax, double* ay, double* ap, hipStream_t st);
 // per-block sums of the squared energy-weighted row magnitudes |b| + |A| |x|
 hipError_t launch_residual_magnitude(const Geom& g, Vec3 x, Vec3 b, const double* eb, const double* ep,
                                     double* partial, int* nblk_out, hipStream_t st);

@@ -1990,11 +1990,23 @@ tph_status tph_apply(tph_solver* s, const double* vx, const double* vy, const do
     g_last_error.clear();
     TPH_TRY(require_ready(s));
     if (!vx || !vy || !p || !ax || !ay || !ap) { set_error("all six arrays are required"); return TPH_ERR_INVALID; }
-    TPH_TRY(load_solution(s, s->t2, vx, vy, p));
     const LevelBuf& L = s->lev[0];
-    TPH_HIP(launch_outer_residual(L.g, vec3(s, s->t2), nullptr, L.eb64, L.ep64, vec3(s, s->t1), ResMode::kApply,
-                                  false, nullptr, nullptr, s->st));
-    TPH_TRY(store_solution(s, s->t1, ax, ay, ap));
+    // straight between the caller's arrays, unless an output shares memory with
+    // another array of the call: then the inputs are copied out of the way first
+    const uintptr_t bytes = (uintptr_t)(L.g.ny + 2) * (L.g.nx + 2) * sizeof(double);
+    const uintptr_t at[6] = {(uintptr_t)ax, (uintptr_t)ay, (uintptr_t)ap, (uintptr_t)vx, (uintptr_t)vy, (uintptr_t)p};
+    bool apart = true;
+    for (int a = 0; a < 3; ++a)
+        for (int b = a + 1; b < 6; ++b) apart = apart && (at[a] + bytes <= at[b] || at[b] + bytes <= at[a]);
+    if (apart) {
+        TPH_HIP(launch_apply_dense(L.g, vx, vy, p, L.eb64, L.ep64, ax, ay, ap, s->st));
+    } else {
+        TPH_TRY(load_solution(s, s->t2, vx, vy, p));
+        TPH_HIP(hipMemsetAsync(s->t1, 0, s->n3 * sizeof(double), s->st));
+        TPH_HIP(launch_outer_residual(L.g, vec3(s, s->t2), nullptr, L.eb64, L.ep64, vec3(s, s->t1), ResMode::kApply,
+                                      false, nullptr, nullptr, s->st));
+        TPH_TRY(store_solution(s, s->t1, ax, ay, ap));
+    }
     TPH_HIP(hipStreamSynchronize(s->st));
     return TPH_OK;
 }
