@@ -2,19 +2,17 @@
 // Between Markers and Grid", Sec. "Advection of Lagrangian Markers",
 // eq. rk4_method), behind the tph_markers_* entry points of tephra.h.
 //
-// Marker -> grid without atomics: markers are binned by the node-grid cell
-// that contains them (the cell whose four corners are the nodes they weight)
-// with a stable least-significant-digit radix sort of (cell, marker) pairs
-// written here (8-bit digits, one pass per digit; see k_digit_count); each
-// cell then sums, in sorted order, the weighted values and weights its
-// markers give to its four corners, and each node adds the partial sums of
-// its (up to) four cells in a fixed order.  Every sum has one writer and a
-// fixed order, so results are bitwise reproducible.  Grid -> marker and RK4
-// are one thread per marker; all four RK4 stages run in registers, the
-// velocity grids are read through the caches.
+// Marker -> grid: markers are binned by the node-grid cell that contains them
+// (the cell whose four corners are the nodes they weight) with a stable
+// two-level partition written here (see k_keys); each cell then sums, in
+// sorted order, the weighted values and weights its markers give to its four
+// corners, and each node adds the sums of its (up to) four cells in a fixed
+// order.  Every sum has one writer and a fixed order, so results are bitwise
+// reproducible.  Grid -> marker and RK4 are one thread per marker; all four
+// RK4 stages run in registers, the velocity grids are read through the caches.
 #include <hip/hip_runtime.h>
 
-#include <climits>
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <string>
@@ -30,12 +28,10 @@ struct tph_markers {
     hipStream_t st = nullptr;
     uint32_t* keys[2] = {nullptr, nullptr};
     int32_t* vals[2] = {nullptr, nullptr};
-    int32_t* hist = nullptr;       // radix sort: per-(digit, tile) counts, then their scan
-    int32_t* chunk = nullptr;      // radix sort: scan of the per-chunk totals of hist
-    int32_t* cstart = nullptr;     // per cell: first sorted position
-    int32_t* cend = nullptr;       // one past the last
-    double* partial = nullptr;     // per cell: 4 corners x (sum w phi, sum w)
-    int sorted = 0;                // which key/value buffer holds the sorted pairs
+    int32_t* hist = nullptr;       // per (tile, digit) counts, then their scan over the tiles
+    int32_t* total = nullptr;      // per digit
+    int32_t* cstart = nullptr;     // per cell: first sorted position; one entry past the last cell
+    const int32_t* order = nullptr;  // the sorted markers: one of vals
     // the current binning
     int kind = -1;
     int n = 0;
@@ -81,287 +77,652 @@ __device__ __forceinline__ uint32_t cell_key(const NodeGrid& q, int nx, int ny, 
     return (uint32_t)(i * (nx + 1) + j);
 }
 
-__global__ __launch_bounds__(256) void k_bin(NodeGrid q, int nx, int ny, int n, const double* __restrict__ xm,
-                                             const double* __restrict__ ym, uint32_t* __restrict__ keys,
-                                             int32_t* __restrict__ vals) {
-    const int m = blockIdx.x * blockDim.x + threadIdx.x;
-    if (m >= n) return;
-    keys[m] = cell_key(q, nx, ny, xm[m], ym[m]);
-    vals[m] = m;
-}
-
 // ---------------------------------------------------------------------------
-// Stable radix sort of (key, marker) pairs, 8-bit digits, least significant
-// first.  A tile of kTile = 4096 pairs goes to one workgroup of 4 waves; wave
-// w owns pairs [w * 1024, (w + 1) * 1024) of its tile and walks them in 16
-// rounds of 64 consecutive pairs.  In a round, the lanes holding the same
-// digit find each other with 8 ballots (one per digit bit); a lane's rank
-// among them is the number of such lanes below it, added to the wave's
-// running count of that digit (kept in LDS, bumped by the highest lane of
-// each group).  Ranks therefore follow the pair order, which makes the sort
-// stable, and no atomic operation is involved.
-//   k_digit_count:  per tile, the count of each digit -> hist[d * ntiles + t]
-//   k_scan_chunks / k_scan_top: exclusive scan of hist in that (digit-major)
-//                   order, as per-chunk scans plus a scan of the chunk totals
-//   k_digit_scatter: ranks again, then writes each pair to
-//                   scan[d * ntiles + t] + (its rank in the tile)
+// Binning: a stable partition of the marker indices by cell, in two levels.
+// The cells (row-major) are cut into buckets of 2^s consecutive ones.
+//   k_keys / k_digit_count: the markers of a tile (one workgroup, 16 waves of
+//                   R rounds of 64 consecutive markers) per bucket -> hist
+//   k_digit_offsets: per bucket, the scan over the tiles, and the total
+//   k_digit_scatter: each marker to its bucket, in marker order
+//   k_cell_sort:    one workgroup per bucket sorts its markers by cell within
+//                   LDS counters and writes the first position of each cell
+// A marker's rank among the earlier ones of its digit comes from ballots and
+// from counts that each wave keeps in LDS, never from the order in which
+// atomic operations arrive (the only atomics are integer counts, where the
+// order does not matter): the order within a cell is that of the markers and
+// results are bitwise reproducible.
+// Bound by memory: per marker 16 B of position and a 4 B key written, read
+// again, 6 B scattered and read, 4 B written.  A least-significant-digit
+// sort over the whole key needs a pass of the pairs per 8 bits (three at
+// 1024^2 cells) and another one for the ranges of the cells.
 // ---------------------------------------------------------------------------
-constexpr int kWaves = 4;
-constexpr int kRounds = 16;
-constexpr int kTile = kWaves * kRounds * 64;     // 4096 pairs per workgroup
-constexpr int kChunk = 4096;                     // scan chunk (entries)
+constexpr int kWaves = 16;
 
-// Counts of the 256 digits over this wave's 1024 pairs of tile t, and (when
-// rank is non-null) each pair's rank among the wave's pairs of its digit.
-__device__ __forceinline__ void wave_rank(const uint32_t* __restrict__ keys, int n, int t, int shift,
-                                          int* __restrict__ wcnt, uint32_t* dig, int* rank) {
+// entry i of an array below 4 GiB (at most 2^28 markers of up to 8 B): uniform base, 32-bit offset
+template <typename T>
+__device__ __forceinline__ const T& at32(const T* base, uint32_t i) {
+    return *(const T*)((const char*)base + i * (uint32_t)sizeof(T));
+}
+template <typename T>
+__device__ __forceinline__ T& at32(T* base, uint32_t i) {
+    return *(T*)((char*)base + i * (uint32_t)sizeof(T));
+}
+
+constexpr int kSortRounds = 20;                  // k_cell_sort: markers of a bucket held at once, per lane
+constexpr int kMaxShift = 11;                    // 2^11 cells a bucket: counts of 8 waves in 32 KB of LDS
+constexpr int kMinShift = 5;
+constexpr int kMaxBuckets = 2304;                // a 2048^2 grid in one pass (83 KB of LDS)
+constexpr int kDigitBits = 12;                   // of a digit of a pass: below kMaxBuckets
+
+// Lanes of `all` that hold the same digit (below 2^NB) as this one: four instructions a bit and no branch
+// (a loop over the bits that are used took twice as long).
+template <int NB>
+__device__ __forceinline__ uint64_t digit_peers_bits(uint32_t d, uint64_t all) {
+    uint32_t lo = (uint32_t)all, hi = (uint32_t)(all >> 32);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        const int32_t m = (int32_t)(d << (31 - b)) >> 31;
+        const uint64_t bal = __ballot(m < 0);
+        lo &= ~((uint32_t)bal ^ (uint32_t)m);
+        hi &= ~((uint32_t)(bal >> 32) ^ (uint32_t)m);
+    }
+    return ((uint64_t)hi << 32) | lo;
+}
+
+// The same where few digits are likely.  Markers mostly come nearly in cell order, and then a wave holds a handful of digits: up to four are
+// matched one by one, what is left bit by bit.
+__device__ __forceinline__ uint64_t digit_peers(uint32_t d, bool valid) {
+    uint64_t rest = __ballot(valid), peers = 0;
+    const uint64_t all = rest;
+#pragma unroll
+    for (int it = 0; it < 4; ++it) {
+        if (!rest) return peers;
+        const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d, __builtin_ctzll(rest));
+        const uint64_t same = __ballot(valid && d == d0);
+        if (d == d0) peers = same;
+        rest &= ~same;
+    }
+    if (!rest) return peers;
+    return digit_peers_bits<kDigitBits>(d, all);
+}
+
+// Rank of this lane's item among the wave's earlier ones of its digit; cnt[d] (this wave's counts in LDS)
+// is advanced.  FEW: a wave is likely to hold few digits.  Every lane of a group reads the count before the group's highest lane advances it: a
+// wave's LDS operations complete in program order.
+template <bool FEW>
+__device__ __forceinline__ uint32_t wave_rank(uint32_t d, bool valid, int nbits, uint16_t* cnt) {
+    const uint32_t base = cnt[d];
+    const uint64_t peers = FEW          ? digit_peers(d, valid)
+                           : nbits <= 9 ? digit_peers_bits<9>(d, __ballot(valid))
+                                        : digit_peers_bits<kMaxShift>(d, __ballot(valid));
+    const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(peers >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)peers, 0u));
+    const uint32_t all = (uint32_t)__popcll(peers);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if (valid && below + 1 == all) cnt[d] = (uint16_t)(base + all);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    return base + below;
+}
+
+// count of one digit per lane into hist (LDS): one addition per distinct digit while there are few
+__device__ __forceinline__ void count_digit(uint32_t d, bool valid, int* hist) {
+    const int lane = threadIdx.x & 63;
+    uint64_t rest = __ballot(valid);
+#pragma unroll
+    for (int it = 0; it < 4; ++it) {
+        if (!rest) return;
+        const int first = __builtin_ctzll(rest);
+        const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d, first);
+        const uint64_t same = __ballot(valid && d == d0);
+        if (lane == first) atomicAdd(&hist[d0], __popcll(same));
+        rest &= ~same;
+    }
+    if ((rest >> lane) & 1ull) atomicAdd(&hist[d], 1);
+}
+
+// exclusive scan over the workgroup's threads (NW waves) of one value each; ws: NW ints of LDS.  All call.
+template <int NW>
+__device__ __forceinline__ int block_exclusive(int v, int* ws) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const uint64_t below = lane ? ((1ull << lane) - 1ull) : 0ull;
+    int s = v;
 #pragma unroll
-    for (int k = 0; k < kRounds; ++k) {
-        const long long m = (long long)t * kTile + (long long)w * (kRounds * 64) + k * 64 + lane;
-        const bool valid = m < n;
-        const uint32_t d = valid ? (keys[m] >> shift) & 255u : 0u;
-        uint64_t peers = __ballot(valid);
-#pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            const uint64_t bal = __ballot((d >> b) & 1u);
-            peers &= ((d >> b) & 1u) ? bal : ~bal;
-        }
-        // every lane of a group reads the count before its highest lane advances it: the read
-        // precedes the write in program order, and a wave's LDS operations complete in order
-        const int base = valid ? wcnt[d] : 0;
-        if (dig) dig[k] = d;
-        if (rank) rank[k] = base + __popcll(peers & below);
-        if (valid && 63 - __clzll(peers) == lane) wcnt[d] = base + __popcll(peers);
+    for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(s, o);
+        if (lane >= o) s += t;
     }
+    if (lane == 63) ws[w] = s;
+    __syncthreads();
+    int before = 0;
+#pragma unroll
+    for (int q = 0; q < NW; ++q) before += q < w ? ws[q] : 0;
+    __syncthreads();
+    return before + s - v;
 }
 
-__global__ __launch_bounds__(256) void k_digit_count(const uint32_t* __restrict__ keys, int n, int ntiles, int shift,
-                                                     int32_t* __restrict__ hist) {
-    __shared__ int cnt[kWaves][256];
-    const int w = threadIdx.x >> 6;
-    for (int d = threadIdx.x; d < kWaves * 256; d += blockDim.x) (&cnt[0][0])[d] = 0;
+// Keys of the markers of a tile, and its counts of the first digit.  1024^2 cells, 16 markers each:
+// 64 us, 5.2 TB/s (x, y and the keys: 335 MB).
+template <int R>
+__global__ __launch_bounds__(1024) void k_keys(NodeGrid q, int nx, int ny, int n, const double* __restrict__ xm,
+                                               const double* __restrict__ ym, int shift, uint32_t mask, int ndig,
+                                               uint32_t* __restrict__ keys, int32_t* __restrict__ hist) {
+    __shared__ int cnt[kMaxBuckets];
+    for (int d = threadIdx.x; d < ndig; d += 1024) cnt[d] = 0;
     __syncthreads();
-    wave_rank(keys, n, blockIdx.x, shift, cnt[w], nullptr, nullptr);
-    __syncthreads();
-    const int d = threadIdx.x;                       // 256 threads: one digit each
-    int tot = 0;
-#pragma unroll
-    for (int q = 0; q < kWaves; ++q) tot += cnt[q][d];
-    hist[(size_t)d * ntiles + blockIdx.x] = tot;
-}
-
-// exclusive scan of each chunk of kChunk entries in place; chunk totals to sums
-__global__ __launch_bounds__(256) void k_scan_chunks(int32_t* __restrict__ a, long long len,
-                                                     int32_t* __restrict__ sums) {
-    __shared__ int part[256];
-    const long long base = (long long)blockIdx.x * kChunk + threadIdx.x * (kChunk / 256);
-    int v[kChunk / 256];
-    int s = 0;
-#pragma unroll
-    for (int q = 0; q < kChunk / 256; ++q) {
-        v[q] = base + q < len ? a[base + q] : 0;
-        s += v[q];
-    }
-    part[threadIdx.x] = s;
-    __syncthreads();
-    // inclusive Hillis-Steele scan of the 256 thread totals
-    for (int off = 1; off < 256; off <<= 1) {
-        const int add = threadIdx.x >= off ? part[threadIdx.x - off] : 0;
-        __syncthreads();
-        part[threadIdx.x] += add;
-        __syncthreads();
-    }
-    int run = part[threadIdx.x] - s;                 // exclusive prefix of this thread
-#pragma unroll
-    for (int q = 0; q < kChunk / 256; ++q) {
-        if (base + q < len) a[base + q] = run;
-        run += v[q];
-    }
-    if (threadIdx.x == 255) sums[blockIdx.x] = part[255];
-}
-
-// exclusive scan of the chunk totals (at most kChunk of them), one workgroup
-__global__ __launch_bounds__(256) void k_scan_top(int32_t* __restrict__ sums, int nchunks) {
-    __shared__ int part[256];
-    const int per = kChunk / 256;
-    int v[kChunk / 256];
-    int s = 0;
-#pragma unroll
-    for (int q = 0; q < per; ++q) {
-        const int i = threadIdx.x * per + q;
-        v[q] = i < nchunks ? sums[i] : 0;
-        s += v[q];
-    }
-    part[threadIdx.x] = s;
-    __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {
-        const int add = threadIdx.x >= off ? part[threadIdx.x - off] : 0;
-        __syncthreads();
-        part[threadIdx.x] += add;
-        __syncthreads();
-    }
-    int run = part[threadIdx.x] - s;
-#pragma unroll
-    for (int q = 0; q < per; ++q) {
-        const int i = threadIdx.x * per + q;
-        if (i < nchunks) sums[i] = run;
-        run += v[q];
-    }
-}
-
-__global__ __launch_bounds__(256) void k_digit_scatter(const uint32_t* __restrict__ kin,
-                                                       const int32_t* __restrict__ vin, int n, int ntiles, int shift,
-                                                       const int32_t* __restrict__ scan,
-                                                       const int32_t* __restrict__ chunk,
-                                                       uint32_t* __restrict__ kout, int32_t* __restrict__ vout) {
-    __shared__ int cnt[kWaves][256];
-    __shared__ int tile_base[kWaves][256];          // global start of each (wave, digit) run
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    for (int d = threadIdx.x; d < kWaves * 256; d += blockDim.x) (&cnt[0][0])[d] = 0;
-    __syncthreads();
-    uint32_t dig[kRounds];
-    int rank[kRounds];
-    wave_rank(kin, n, blockIdx.x, shift, cnt[w], dig, rank);
-    __syncthreads();
-    {
-        const int d = threadIdx.x;
-        const long long e = (long long)d * ntiles + blockIdx.x;
-        int off = scan[e] + chunk[e / kChunk];
+    const long long m0 = ((long long)blockIdx.x * kWaves + w) * (R * 64) + lane;
+    constexpr int U = R < 4 ? R : 4;             // loads of U rounds in flight
 #pragma unroll
-        for (int q = 0; q < kWaves; ++q) {
-            tile_base[q][d] = off;
-            off += cnt[q][d];
+    for (int k0 = 0; k0 < R; k0 += U) {
+        double x[U], y[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const long long m = m0 + (k0 + k) * 64;
+            x[k] = m < n ? xm[m] : 0.0;
+            y[k] = m < n ? ym[m] : 0.0;
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const long long m = m0 + (k0 + k) * 64;
+            const uint32_t key = cell_key(q, nx, ny, x[k], y[k]);
+            if (m < n) keys[m] = key;
+            count_digit((key >> shift) & mask, m < n, cnt);
         }
     }
     __syncthreads();
-#pragma unroll
-    for (int k = 0; k < kRounds; ++k) {
-        const long long m = (long long)blockIdx.x * kTile + (long long)w * (kRounds * 64) + k * 64 + lane;
-        if (m < n) {
-            const int pos = tile_base[w][dig[k]] + rank[k];
-            kout[pos] = kin[m];
-            vout[pos] = vin[m];
-        }
-    }
+    for (int d = threadIdx.x; d < ndig; d += 1024) hist[(size_t)blockIdx.x * ndig + d] = cnt[d];
 }
 
-__global__ __launch_bounds__(256) void k_ranges(int n, const uint32_t* __restrict__ keys, int32_t* __restrict__ cstart,
-                                                int32_t* __restrict__ cend) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= n) return;
-    const uint32_t k = keys[p];
-    if (p == 0 || keys[p - 1] != k) cstart[k] = p;
-    if (p == n - 1 || keys[p + 1] != k) cend[k] = p + 1;
-}
-
-// Per cell, in sorted (stable: marker index) order: sums of w phi and w for
-// its four corners.  A workgroup owns 256 consecutive cells, whose markers
-// occupy one contiguous run of the sorted order.  The run goes through LDS
-// in chunks of kStage markers: the workgroup reads the sorted marker indices
-// and gathers x, y and phi with neighbouring lanes on neighbouring entries;
-// then every thread walks its own cell's part of the chunk from LDS.  The
-// products and sums per cell are those of a direct loop over the cell's
-// markers, in the same order.  Slots are padded by one per 16 entries: the
-// cells of neighbouring lanes start about 16 markers apart, which would
-// otherwise put their reads on the same LDS banks.
-constexpr int kStage = 1024;
-constexpr int kStageSlots = kStage + kStage / 16;
-__device__ __forceinline__ int stage_slot(int t) { return t + (t >> 4); }
-
-__global__ __launch_bounds__(256) void k_cell_partials(NodeGrid q, int nx, int ny, const int32_t* __restrict__ cstart,
-                                                       const int32_t* __restrict__ cend,
-                                                       const int32_t* __restrict__ order,
-                                                       const double* __restrict__ xm, const double* __restrict__ ym,
-                                                       const double* __restrict__ phi, double* __restrict__ partial) {
-    __shared__ double sx[kStageSlots], sy[kStageSlots], sf[kStageSlots];
-    __shared__ int run_lo[4], run_hi[4];
-    const int ncell = (nx + 1) * (ny + 1);
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    const bool live = c < ncell;
-    const int b = live ? cstart[c] : 0, e = live ? cend[c] : 0;     // empty cells: b == e
-    // run of the workgroup: first start and last end over its non-empty cells
-    int lo = b < e ? b : INT_MAX, hi = b < e ? e : 0;
-    for (int o = 32; o > 0; o >>= 1) {
-        lo = min(lo, __shfl_xor(lo, o));
-        hi = max(hi, __shfl_xor(hi, o));
-    }
-    if ((threadIdx.x & 63) == 0) {
-        run_lo[threadIdx.x >> 6] = lo;
-        run_hi[threadIdx.x >> 6] = hi;
+// the same counts of a further digit, from keys already in the order of the earlier one
+template <int R>
+__global__ __launch_bounds__(1024) void k_digit_count(const uint32_t* __restrict__ keys, int n, int shift,
+                                                      uint32_t mask, int ndig, int32_t* __restrict__ hist) {
+    __shared__ int cnt[kMaxBuckets];
+    for (int d = threadIdx.x; d < ndig; d += 1024) cnt[d] = 0;
+    __syncthreads();
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const long long m0 = ((long long)blockIdx.x * kWaves + w) * (R * 64) + lane;
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        const long long m = m0 + k * 64;
+        const uint32_t key = m < n ? keys[m] : 0u;
+        count_digit((key >> shift) & mask, m < n, cnt);
     }
     __syncthreads();
-    const int P0 = min(min(run_lo[0], run_lo[1]), min(run_lo[2], run_lo[3]));
-    const int P1 = max(max(run_hi[0], run_hi[1]), max(run_hi[2], run_hi[3]));
-    const int i = live ? c / (nx + 1) : 0, j = c - i * (nx + 1);
-    const double xj = q.x0 + j * q.dx, yi = q.y0 + i * q.dy;
-    double s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    constexpr int KS = kStage / 256;
-    for (int base = P0; base < P1; base += kStage) {
-        const int cnt = min(kStage, P1 - base);
-        int m[KS];
-#pragma unroll
-        for (int k = 0; k < KS; ++k) {
-            const int t = threadIdx.x + k * 256;
-            m[k] = t < cnt ? order[base + t] : -1;
-        }
-        double vx[KS], vy[KS], vf[KS];
-#pragma unroll
-        for (int k = 0; k < KS; ++k) {
-            vx[k] = m[k] >= 0 ? xm[m[k]] : 0.0;
-            vy[k] = m[k] >= 0 ? ym[m[k]] : 0.0;
-            vf[k] = m[k] >= 0 ? phi[m[k]] : 0.0;
-        }
-#pragma unroll
-        for (int k = 0; k < KS; ++k) {
-            const int t = stage_slot(threadIdx.x + k * 256);
-            sx[t] = vx[k];
-            sy[t] = vy[k];
-            sf[t] = vf[k];
-        }
+    for (int d = threadIdx.x; d < ndig; d += 1024) hist[(size_t)blockIdx.x * ndig + d] = cnt[d];
+}
+
+// hist (tile-major: ndig counts per tile) -> per digit the exclusive scan over the tiles, in place, and its
+// total.  16 digits per workgroup (64 B of a row), 64 runs of tiles.
+__global__ __launch_bounds__(1024) void k_digit_offsets(int32_t* __restrict__ hist, int ntiles, int ndig,
+                                                        int32_t* __restrict__ total) {
+    __shared__ int part[64][17];
+    const int c = threadIdx.x & 15, g = threadIdx.x >> 4;
+    const int d = blockIdx.x * 16 + c;
+    const bool live = d < ndig;
+    const int per = (ntiles + 63) / 64;
+    const int t0 = min(g * per, ntiles), t1 = min(t0 + per, ntiles);
+    int s = 0;
+    if (live) {
+#pragma unroll 8
+        for (int t = t0; t < t1; ++t) s += hist[(size_t)t * ndig + d];
+    }
+    part[g][c] = s;
+    __syncthreads();
+    for (int o = 1; o < 64; o <<= 1) {
+        const int add = g >= o ? part[g - o][c] : 0;
         __syncthreads();
-        const int pe = min(e, base + cnt);
-        for (int p = max(b, base); p < pe; ++p) {
-            const int t = stage_slot(p - base);
-            const double rx = (sx[t] - xj) / q.dx, ry = (sy[t] - yi) / q.dy;
-            const double f = sf[t];
-            const double w00 = (1.0 - rx) * (1.0 - ry), w01 = rx * (1.0 - ry), w10 = (1.0 - rx) * ry, w11 = rx * ry;
-            s[0] += w00 * f;
-            s[1] += w00;
-            s[2] += w01 * f;
-            s[3] += w01;
-            s[4] += w10 * f;
-            s[5] += w10;
-            s[6] += w11 * f;
-            s[7] += w11;
-        }
+        part[g][c] += add;
         __syncthreads();
     }
     if (!live) return;
-    double* out = partial + (size_t)c * 8;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) out[k] = s[k];
+    int run = part[g][c] - s;
+#pragma unroll 8
+    for (int t = t0; t < t1; ++t) {
+        const int v = hist[(size_t)t * ndig + d];
+        hist[(size_t)t * ndig + d] = run;
+        run += v;
+    }
+    if (g == 63) total[d] = part[g][c];
 }
 
-// node (i, j) = corner (1,1) of cell (i-1, j-1), (1,0) of (i-1, j), (0,1) of (i, j-1), (0,0) of (i, j)
-__global__ __launch_bounds__(256) void k_nodes(NodeGrid q, int nx, int ny, const double* __restrict__ partial,
-                                               double fill, double* __restrict__ grid) {
-    const int j = q.jmin + (int)(blockIdx.x * blockDim.x + threadIdx.x);
-    const int i = q.imin + (int)blockIdx.y;
-    if (j > q.jmax || i > q.imax) return;
-    double num = 0.0, den = 0.0;
-    const int ci[4] = {i - 1, i - 1, i, i};
-    const int cj[4] = {j - 1, j, j - 1, j};
-    const int corner[4] = {3, 2, 1, 0};
+// Each marker to its digit's run: position = start of the digit + its earlier tiles + earlier waves + rank.
+// K is uint16_t where this is the only pass (the bits below the digit are kept: all that k_cell_sort
+// needs), uint32_t (whole keys) otherwise.  vin == nullptr: the markers are in their own order.
+template <int R, typename K>
+__global__ __launch_bounds__(1024, 8) void k_digit_scatter(const uint32_t* __restrict__ kin,
+                                                        const int32_t* __restrict__ vin, int n, int shift,
+                                                        uint32_t mask, int ndig,
+                                                        const int32_t* __restrict__ hist,
+                                                        const int32_t* __restrict__ total, K* __restrict__ kout,
+                                                        int32_t* __restrict__ vout) {
+    extern __shared__ int lds[];
+    __shared__ int ws[kWaves];
+    int* base = lds;                                                   // [ndig]
+    uint16_t* wcnt = (uint16_t*)(lds + ndig);                          // [kWaves][ndig]
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const uint32_t tile0 = blockIdx.x * (uint32_t)(kWaves * R * 64);
+    const int left = min(n - (int)tile0, kWaves * R * 64);             // markers of the tile
+    const int m0 = w * (R * 64) + lane;                                // within the tile
+    uint32_t key[R], at[R];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        if (ci[k] < 0 || ci[k] > ny || cj[k] < 0 || cj[k] > nx) continue;
-        const double* pp = partial + ((size_t)ci[k] * (nx + 1) + cj[k]) * 8 + 2 * corner[k];
-        num += pp[0];
-        den += pp[1];
+    for (int k = 0; k < R; ++k) key[k] = m0 + k * 64 < left ? at32(kin + tile0, m0 + k * 64) : 0u;
+    for (int d = threadIdx.x; d < ndig * (kWaves / 2); d += 1024) ((uint32_t*)wcnt)[d] = 0u;
+    {
+        constexpr int P = (kMaxBuckets + 1023) / 1024;
+        int v[P], s = 0;
+        const int d0 = threadIdx.x * P;
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            v[p] = d0 + p < ndig ? total[d0 + p] : 0;
+            s += v[p];
+        }
+        int run = block_exclusive<kWaves>(s, ws);
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            if (d0 + p < ndig) base[d0 + p] = run + hist[(size_t)blockIdx.x * ndig + d0 + p];
+            run += v[p];
+        }
     }
-    grid[(size_t)i * q.pitch + j] = den > 0.0 ? num / den : fill;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        const uint32_t d = (key[k] >> shift) & mask;
+        at[k] = wave_rank<true>(d, m0 + k * 64 < left, 0, wcnt + w * ndig);
+        __builtin_amdgcn_sched_barrier(0);       // one round at a time: their temporaries together do not fit
+    }
+    __syncthreads();
+    for (int d = threadIdx.x; d < ndig; d += 1024) {
+        uint32_t run = 0;
+#pragma unroll
+        for (int q = 0; q < kWaves; ++q) {
+            const uint32_t c = wcnt[q * ndig + d];
+            wcnt[q * ndig + d] = (uint16_t)run;                        // below 16 R 64 <= 16384
+            run += c;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        const int m = m0 + k * 64;
+        asm("" : "+v"(key[k]));                  // the digit anew: 16 digits and addresses kept would spill
+        if (m < left) {
+            const uint32_t d = (key[k] >> shift) & mask;
+            const uint32_t pos = (uint32_t)base[d] + wcnt[w * ndig + d] + at[k];
+            at32(kout, pos) = sizeof(K) == 2 ? (K)(key[k] & ((1u << shift) - 1u)) : (K)key[k];
+            at32(vout, pos) = vin ? at32(vin + tile0, m) : (int32_t)(tile0 + m);
+        }
+    }
+}
+
+// first position whose key is at least `key`
+__device__ __forceinline__ int lower_bound(const uint32_t* __restrict__ keys, int n, uint64_t key) {
+    int lo = 0, hi = n;
+    while (lo < hi) {
+        const int mid = lo + ((hi - lo) >> 1);
+        if (keys[mid] < key) lo = mid + 1;
+        else hi = mid;
+    }
+    return lo;
+}
+
+// Markers of one bucket (2^shift cells) to the order of the cells, and cstart of its cells.  A bucket of
+// up to 10240 markers is ranked once, in registers; a longer one is counted first and goes in pieces.
+// K as in k_digit_scatter: the bucket's run comes from the digit totals (uint16_t), or from a search in
+// the sorted keys (uint32_t).
+template <int NW, typename K>
+__global__ __launch_bounds__(NW * 64, 8) void k_cell_sort(const K* __restrict__ kin, const int32_t* __restrict__ vin, int n,
+                                                    int shift, int ncell, const int32_t* __restrict__ total,
+                                                    int32_t* __restrict__ cstart, int32_t* __restrict__ order) {
+    constexpr int R = kSortRounds;
+    constexpr int NT = NW * 64;
+    constexpr int P = (1 << kMaxShift) / NT;                           // at most that many cells a thread
+    extern __shared__ int lds[];
+    __shared__ int ws[NW];
+    __shared__ int range[2];
+    const int L = 1 << shift;
+    int* base = lds;                                                   // [L]
+    uint16_t* wcnt = (uint16_t*)(lds + L);                             // [NW][L]
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int c0 = (int)blockIdx.x << shift;
+    const int nc = min(L, ncell - c0);
+    int p0, cnt;
+    if (sizeof(K) == 2) {
+        int s = 0;
+        for (int d = threadIdx.x; d < (int)blockIdx.x; d += NT) s += n ? total[d] : 0;
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+        if (lane == 0) ws[w] = s;
+        __syncthreads();
+        p0 = 0;
+#pragma unroll
+        for (int q = 0; q < NW; ++q) p0 += ws[q];
+        cnt = n ? total[blockIdx.x] : 0;
+    } else {
+        if (threadIdx.x < 2)
+            range[threadIdx.x] = lower_bound((const uint32_t*)kin, n, ((uint64_t)blockIdx.x + threadIdx.x) << shift);
+        __syncthreads();
+        p0 = range[0];
+        cnt = range[1] - p0;
+    }
+    const uint32_t mask = (uint32_t)L - 1u;
+    const int per = (L + NT - 1) / NT;                                 // cells of a thread: consecutive ones
+    const int mine = threadIdx.x * per;
+    // positions of the cells from their counts; cstart
+    auto place = [&](const int* tot) {
+        int s = 0;
+#pragma unroll
+        for (int p = 0; p < P; ++p) s += tot[p];
+        int run = p0 + block_exclusive<NW>(s, ws);
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            if (p < per && mine + p < L) base[mine + p] = run;
+            if (p < per && mine + p < nc) cstart[c0 + mine + p] = run;
+            run += tot[p];
+        }
+    };
+    if (threadIdx.x == 0 && c0 + nc == ncell) cstart[ncell] = n;
+    const bool pieces = cnt > NW * R * 64;
+    if (pieces) {
+        for (int c = threadIdx.x; c < L; c += NT) base[c] = 0;
+        __syncthreads();
+        for (int t = threadIdx.x; t < cnt; t += NT) atomicAdd(&base[(uint32_t)kin[p0 + t] & mask], 1);
+        __syncthreads();
+        int tot[P];
+#pragma unroll
+        for (int p = 0; p < P; ++p) tot[p] = p < per && mine + p < L ? base[mine + p] : 0;
+        place(tot);
+    }
+    int t0 = 0;
+    do {
+        const int left = min(cnt - t0, NW * R * 64);
+        const int rounds = (left + NW * 64 - 1) / (NW * 64);   // at most R
+        const int m0 = w * rounds * 64 + lane;                         // within the piece
+        for (int c = threadIdx.x; c < L * (NW / 2); c += NT) ((uint32_t*)wcnt)[c] = 0u;
+        uint32_t it[R];                                                // cell | rank within the wave << 16
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            it[k] = 0u;
+            if (k < rounds && m0 + k * 64 < left) it[k] = (uint32_t)at32(kin + p0 + t0, m0 + k * 64) & mask;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            if (k < rounds) it[k] |= wave_rank<false>(it[k], m0 + k * 64 < left, shift, wcnt + w * L) << 16;
+            __builtin_amdgcn_sched_barrier(0);   // as in k_digit_scatter
+        }
+        __syncthreads();
+        int tot[P];
+        int own = mine;
+        asm("" : "+v"(own));                     // no addresses kept over the pieces
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            uint32_t run = 0;
+            if (p < per && own + p < L) {
+#pragma unroll
+                for (int q = 0; q < NW; ++q) {
+                    const uint32_t c = wcnt[q * L + own + p];
+                    wcnt[q * L + own + p] = (uint16_t)run;             // below 10240
+                    run += c;
+                }
+            }
+            tot[p] = (int)run;
+        }
+        if (!pieces) place(tot);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            const int t = m0 + k * 64;
+            asm("" : "+v"(it[k]));                                     // as in k_digit_scatter
+            if (k < rounds && t < left) {
+                const uint32_t c = it[k] & 0xffffu;
+                at32(order, (uint32_t)base[c] + wcnt[w * L + c] + (it[k] >> 16)) = at32(vin + p0 + t0, t);
+            }
+        }
+        t0 += left;
+        if (t0 < cnt) {                                                // the same for every thread
+            __syncthreads();
+#pragma unroll
+            for (int p = 0; p < P; ++p)
+                if (p < per && mine + p < L) base[mine + p] += tot[p];
+        }
+    } while (t0 < cnt);
+}
+
+// Factors rx, ry of a marker's weights in its cell: the quotients of the direct formulas.  Those by the
+// spacing are had from its reciprocal and two corrections (a third of a division's operations); the
+// cell column by a product, unless that is so close to a column's edge, or so far out, that the division
+// that gave the key might say otherwise: then (false) everything is to be divided.
+__device__ __forceinline__ double by_spacing(double a, double h, double ih) {
+    double v = a * ih;
+    v = __builtin_fma(__builtin_fma(-h, v, a), ih, v);
+    return __builtin_fma(__builtin_fma(-h, v, a), ih, v);
+}
+
+__device__ __forceinline__ bool factors(const NodeGrid& q, int nx, double x, double y, double yi, double& rx,
+                                        double& ry) {
+    const double t = (x - q.x0) * q.idx;
+    int j = (int)floor(t);
+    j = j < 0 ? 0 : (j > nx ? nx : j);
+    rx = by_spacing(x - (q.x0 + j * q.dx), q.dx, q.idx);
+    ry = by_spacing(y - yi, q.dy, q.idy);
+    return fabs(t - rint(t)) > 0x1p-20 && fabs(y - yi) < 0x1p40 * q.dy;  // false for NaN
+}
+
+__device__ __forceinline__ void divided_factors(const NodeGrid& q, int nx, double x, double y, double yi, double& rx,
+                                                double& ry) {
+    int j = (int)floor((x - q.x0) / q.dx);
+    j = j < 0 ? 0 : (j > nx ? nx : j);
+    rx = (x - (q.x0 + j * q.dx)) / q.dx;
+    ry = (y - yi) / q.dy;
+}
+
+// ---------------------------------------------------------------------------
+// Averages on the nodes from the sorted markers.  Per cell, in sorted order:
+// sums of w phi and w for its four corners; node (i, j) = corner (1,1) of
+// cell (i-1, j-1), (1,0) of (i-1, j), (0,1) of (i, j-1), (0,0) of (i, j), in
+// that order.  A wave takes 64 neighbouring cells of R rows, 16 at a time:
+// their markers are one run of the sorted order.
+//   Its markers, one per lane, are gathered, their positions become the two
+// factors of the weights, and both go to LDS with phi; then four lanes walk
+// each cell's markers, one corner each (5 operations a marker instead of 16
+// on a quarter of the lanes).  The gathers of the next 16 cells are in flight
+// meanwhile.  Slots are padded by one per 16: neighbouring cells start
+// about 16 markers apart, which would otherwise put their reads on the same
+// LDS banks.
+//   The sums of a row go through LDS once, to the lanes of the nodes; the row
+// above's are kept in registers, those of the wave before come through
+// LDS.  Lane 0 of a wave is a cell for the node of lane 1 only, and a
+// workgroup's first cell row is the last one of the workgroup above.
+// Bound by the gathers (28 B a marker) and, nearly as much, by the vector
+// operations.
+// ---------------------------------------------------------------------------
+constexpr int kNodeWaves = 4;
+__device__ __forceinline__ int stage_slot(int t) { return t + (t >> 4); }
+
+// every node of the range, where there are no markers
+__global__ __launch_bounds__(256) void k_fill_nodes(NodeGrid q, double fill, double* __restrict__ grid) {
+    const int j = q.jmin + (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (j <= q.jmax) grid[(size_t)(q.imin + (int)blockIdx.y) * q.pitch + j] = fill;
+}
+
+// H: markers a lane holds, 64 H the piece that is staged at once
+template <int R, int H>
+__global__ __launch_bounds__(kNodeWaves * 64) void k_nodes(NodeGrid q, int nx, int ny,
+                                                           const int32_t* __restrict__ cstart,
+                                                           const int32_t* __restrict__ order,
+                                                           const double* __restrict__ xm,
+                                                           const double* __restrict__ ym,
+                                                           const double* __restrict__ phi, double fill,
+                                                           double* __restrict__ grid) {
+    constexpr int kChunk = H * 64;
+    constexpr int kSlots = kChunk + kChunk / 16 + 4;                   // an even number, past the walk's last read
+    __shared__ double stage[kNodeWaves][3 * kSlots];
+    __shared__ double2 corners[kNodeWaves][4][64];                     // (sum w phi, sum w) of a row's cells
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    double* sx = stage[w];
+    double* sy = sx + kSlots;
+    double* sf = sy + kSlots;
+    const int jl = (int)blockIdx.x * 63 - 1;                           // cell column of lane 0
+    const int j = jl + lane;
+    const int i0 = (int)blockIdx.y * (kNodeWaves * R - 1) - 1 + w * R; // first cell row of the wave
+    const bool col = j >= 0 && j <= nx;
+    const int corner = lane & 3;
+    // weight of this lane's corner: (ax + bx rx)(ay + by ry), that is 1 - r or r
+    const double ax = corner & 1 ? 0.0 : 1.0, bx = corner & 1 ? 1.0 : -1.0;
+    const double ay = corner & 2 ? 0.0 : 1.0, by = corner & 2 ? 1.0 : -1.0;
+    // cell ranges of a row; columns and rows outside are empty, at the end or the start of their neighbours'
+    auto range = [&](int i, int& b, int& e) {
+        const bool live = i >= 0 && i <= ny;
+        const uint32_t c = (uint32_t)i * (uint32_t)(nx + 1);
+        b = live ? at32(cstart, c + (uint32_t)min(max(j, 0), nx + 1)) : 0;
+        e = live ? at32(cstart, c + (uint32_t)min(max(j + 1, 0), nx + 1)) : 0;
+    };
+    int b, e, b1, e1;                                                  // this row's, the next one's
+    int m[H];
+    double vx[H], vy[H], vf[H];
+    // straight-line code: with a branch around a round, each would wait for the one before.  A lane past the
+    // run takes its last marker (some marker, if the run is empty).
+    auto indices = [&](int P0, int P1) {
+#pragma unroll
+        for (int k = 0; k < H; ++k) m[k] = at32(order, min(P0 + k * 64 + lane, max(P1 - 1, 0)));
+    };
+    auto gather = [&]() {
+#pragma unroll
+        for (int k = 0; k < H; ++k) {
+            vx[k] = at32(xm, m[k]);
+            vy[k] = at32(ym, m[k]);
+            vf[k] = at32(phi, m[k]);
+        }
+    };
+    auto to_lds = [&](double yi) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        double rx[H], ry[H];
+        bool unsure = false;
+#pragma unroll
+        for (int k = 0; k < H; ++k) unsure |= !factors(q, nx, vx[k], vy[k], yi, rx[k], ry[k]);
+        if (unsure) {
+#pragma unroll
+            for (int k = 0; k < H; ++k) divided_factors(q, nx, vx[k], vy[k], yi, rx[k], ry[k]);
+        }
+#pragma unroll
+        for (int k = 0; k < H; ++k) {
+            const int t = stage_slot(lane + k * 64);
+            sx[t] = rx[k];
+            sy[t] = ry[k];
+            sf[t] = vf[k];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    };
+    double num, den;
+    auto add = [&](double rx, double ry, double f) {
+        const double wt = __builtin_fma(bx, rx, ax) * __builtin_fma(by, ry, ay);
+        num = __builtin_fma(wt, f, num);
+        den += wt;
+    };
+    // positions [u, ue) of the run from P0, two at a time, the next two's reads ahead of these two's sums
+    auto walk = [&](int u, int ue, int P0) {
+        if (u >= ue) return;
+        int t = stage_slot(u - P0), t1 = stage_slot(u + 1 - P0);
+        double rx = sx[t], ry = sy[t], f = sf[t], rx1 = sx[t1], ry1 = sy[t1], f1 = sf[t1];
+        while (u + 1 < ue) {
+            u += 2;
+            t = stage_slot(u - P0);
+            t1 = stage_slot(u + 1 - P0);
+            const double nx0 = sx[t], ny0 = sy[t], nf0 = sf[t], nx1 = sx[t1], ny1 = sy[t1], nf1 = sf[t1];
+            add(rx, ry, f);
+            add(rx1, ry1, f1);
+            rx = nx0;
+            ry = ny0;
+            f = nf0;
+            rx1 = nx1;
+            ry1 = ny1;
+            f1 = nf1;
+        }
+        if (u < ue) add(rx, ry, f);
+    };
+    auto run_of = [&](int g, int bb, int ee, int& P0, int& P1) {
+        P0 = __builtin_amdgcn_readlane(bb, g * 16);
+        P1 = __builtin_amdgcn_readlane(ee, g * 16 + 15);
+    };
+    double2 up[2], top[2];                                             // corners 3, 2 of the row above; 1, 0 of the first row
+    auto node = [&](int i, double2 c1, double2 c0) {
+        double n = up[0].x, d = up[0].y;
+        n += up[1].x;
+        d += up[1].y;
+        n += c1.x;
+        d += c1.y;
+        n += c0.x;
+        d += c0.y;
+        if (lane > 0 && i >= q.imin && i <= q.imax && j >= q.jmin && j <= q.jmax)
+            grid[(size_t)i * q.pitch + j] = d > 0.0 ? n / d : fill;
+    };
+    range(i0, b, e);
+    if (R > 1) range(i0 + 1, b1, e1);
+    int P0, P1;
+    run_of(0, b, e, P0, P1);
+    indices(P0, P1);
+    gather();
+    int N0, N1;
+    run_of(1, b, e, N0, N1);
+    indices(N0, N1);
+#pragma unroll 1
+    for (int gg = 0; gg < 4 * R; ++gg) {
+        const int g = gg & 3, i = i0 + (gg >> 2);
+        const double yi = q.y0 + i * q.dy;
+        const int cb = __shfl(b, g * 16 + (lane >> 2)), ce = __shfl(e, g * 16 + (lane >> 2));
+        // the run after the next one
+        int M0 = 0, M1 = 0;
+        if (g < 2) run_of(g + 2, b, e, M0, M1);
+        else if (gg + 2 < 4 * R) run_of(g - 2, b1, e1, M0, M1);
+        num = den = 0.0;
+        to_lds(yi);
+        if (P1 - P0 <= kChunk) {
+            gather();
+            indices(M0, M1);
+            walk(cb, ce, P0);
+        } else {
+            walk(cb, min(ce, P0 + kChunk), P0);
+            for (int p = P0 + kChunk; p < P1; p += kChunk) {
+                const int pe = min(p + kChunk, P1);
+                indices(p, pe);
+                gather();
+                to_lds(yi);
+                walk(max(cb, p), min(ce, pe), p);
+            }
+            indices(N0, N1);
+            gather();
+            indices(M0, M1);
+        }
+        P0 = N0;
+        P1 = N1;
+        N0 = M0;
+        N1 = M1;
+        corners[w][corner][g * 16 + (lane >> 2)] = make_double2(num, den);
+        if (g == 3) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            const int l1 = max(lane - 1, 0);
+            const double2 c1 = corners[w][1][l1], c0 = corners[w][0][lane];
+            if (gg == 3) {
+                top[0] = c1;
+                top[1] = c0;
+            } else {
+                node(i, c1, c0);
+            }
+            up[0] = corners[w][3][l1];
+            up[1] = corners[w][2][lane];
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            b = b1;
+            e = e1;
+            if (gg + 4 < 4 * R) range(i + 2, b1, e1);
+        }
+    }
+    double2* mine = (double2*)stage[w];
+    mine[lane] = up[0];
+    mine[64 + lane] = up[1];
+    __syncthreads();
+    if (w == 0) return;                                                // its first row's nodes are the workgroup above's
+    const double2* before = (const double2*)stage[w - 1];
+    up[0] = before[lane];
+    up[1] = before[64 + lane];
+    node(i0, top[0], top[1]);
 }
 
 // (the cell found by a multiplication may differ from the divided one for a
@@ -420,13 +781,87 @@ inline unsigned blocks(long long n) { return (unsigned)((n + 255) / 256); }
         }                                                                                            \
     } while (0)
 
-constexpr int kMaxMarkers = 1 << 28;   // keeps the scan of the digit counts within one top-level workgroup
+constexpr int kMaxMarkers = 1 << 28;
 
-int key_bits(const tph_markers* h) {
-    const uint64_t ncell = (uint64_t)(h->nx + 1) * (uint64_t)(h->ny + 1);
-    int b = 1;
-    while (b < 32 && (1ull << b) < ncell) ++b;
-    return b;
+// One cell row a wave while a small grid leaves the chip idle, two on larger ones: an eighth of the rows is then
+// done twice (four rows: 172 us instead of 157 at 1024^2, with too few workgroups for an even last wave).
+constexpr long long kRowCells = 300000;
+
+// How the bits of a key are divided: the lowest `shift` within a bucket, the rest in one pass or two.
+// One pass as long as its counts fit in LDS; two of about equal width beyond 2304 buckets of 2048 cells
+// (grids above 4.7 M cells).
+struct BinPlan {
+    int shift = 0, npass = 1;
+    int buckets = 0;               // of 2^shift cells
+    int bits[2] = {0, 0};          // of each pass
+    int ndig[2] = {0, 0};
+    int most() const { return std::max(ndig[0], ndig[1]); }
+};
+
+BinPlan bin_plan(const tph_markers* h) {
+    const int ncell = (h->nx + 1) * (h->ny + 1);
+    BinPlan p;
+    // as many buckets as one pass can tell apart: with 512 cells each at 1024^2 x 16 markers k_cell_sort takes 92 us, with
+    // 1024 cells 131 us, and the other kernels 8 us less
+    p.shift = kMinShift;
+    auto count = [&] { return (int)(((long long)ncell + (1ll << p.shift) - 1) >> p.shift); };
+    while (p.shift < kMaxShift && count() > kMaxBuckets) ++p.shift;
+    p.buckets = count();
+    int nb = 1;
+    while ((1ll << nb) < p.buckets) ++nb;
+    if (p.buckets <= kMaxBuckets) {
+        p.bits[0] = nb;
+        p.ndig[0] = p.buckets;
+    } else {
+        p.npass = 2;
+        p.bits[0] = nb / 2;
+        p.bits[1] = nb - nb / 2;
+        for (int k = 0; k < 2; ++k) p.ndig[k] = 1 << p.bits[k];
+    }
+    return p;
+}
+
+// Rounds of a tile (kWaves * 64 markers each): few for few markers, so that there is a workgroup for
+// every CU; many for many, which keeps the table of counts (ndig per tile) small against them.
+int tile_rounds(long long n) { return n <= (1 << 18) ? 1 : n <= (1 << 22) ? 4 : 16; }
+long long tiles_of(long long n) {
+    const long long t = (long long)tile_rounds(n) * kWaves * 64;
+    return (n + t - 1) / t;
+}
+
+template <int R>
+hipError_t launch_pass(tph_markers* h, const BinPlan& p, const NodeGrid& q, int pass) {
+    const int ntiles = (int)tiles_of(h->n), n = h->n;
+    const int shift = p.shift + (pass ? p.bits[0] : 0), bits = p.bits[pass], ndig = p.ndig[pass];
+    const uint32_t mask = (1u << bits) - 1u;
+    const size_t lds = (size_t)ndig * (sizeof(int) + kWaves * sizeof(uint16_t));
+    if (pass == 0)
+        hipLaunchKernelGGL((k_keys<R>), dim3(ntiles), dim3(1024), 0, h->st, q, h->nx, h->ny, n, h->xm, h->ym, shift, mask,
+                           ndig, h->keys[0], h->hist);
+    else
+        hipLaunchKernelGGL((k_digit_count<R>), dim3(ntiles), dim3(1024), 0, h->st, h->keys[pass & 1], n, shift, mask, ndig,
+                           h->hist);
+    hipLaunchKernelGGL(k_digit_offsets, dim3((unsigned)((ndig + 15) / 16)), dim3(1024), 0, h->st, h->hist, ntiles, ndig,
+                       h->total);
+    const int32_t* vin = pass ? h->vals[(pass + 1) & 1] : nullptr;
+    if (p.npass == 1)
+        hipLaunchKernelGGL((k_digit_scatter<R, uint16_t>), dim3(ntiles), dim3(1024), lds, h->st, h->keys[0], vin, n, shift,
+                           mask, ndig, h->hist, h->total, (uint16_t*)h->keys[1], h->vals[0]);
+    else
+        hipLaunchKernelGGL((k_digit_scatter<R, uint32_t>), dim3(ntiles), dim3(1024), lds, h->st, h->keys[pass & 1], vin, n,
+                           shift, mask, ndig, h->hist, h->total, h->keys[1 - (pass & 1)], h->vals[pass & 1]);
+    return hipGetLastError();
+}
+
+// kernels whose LDS can exceed 64 KB: granted once per handle, on its device
+hipError_t grant_lds() {
+    const void* f[] = {(const void*)&k_digit_scatter<1, uint16_t>,  (const void*)&k_digit_scatter<4, uint16_t>,
+                       (const void*)&k_digit_scatter<16, uint16_t>, (const void*)&k_cell_sort<8, uint16_t>,
+                       (const void*)&k_cell_sort<8, uint32_t>};
+    hipError_t e = hipSuccess;
+    for (const void* k : f)
+        if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
+    return e;
 }
 
 }  // namespace
@@ -467,12 +902,17 @@ tph_status tph_markers_create(int32_t nx, int32_t ny, double lx, double ly, int3
         get((void**)&h->keys[k], (size_t)capacity * sizeof(uint32_t));
         get((void**)&h->vals[k], (size_t)capacity * sizeof(int32_t));
     }
-    get((void**)&h->cstart, ncell * sizeof(int32_t));
-    get((void**)&h->cend, ncell * sizeof(int32_t));
-    get((void**)&h->partial, ncell * 8 * sizeof(double));
-    const long long ntiles = (capacity + kTile - 1) / kTile;
-    get((void**)&h->hist, (size_t)ntiles * 256 * sizeof(int32_t));
-    get((void**)&h->chunk, (size_t)((ntiles * 256 + kChunk - 1) / kChunk) * sizeof(int32_t));
+    get((void**)&h->cstart, (ncell + 1) * sizeof(int32_t));
+    const BinPlan p = bin_plan(h);
+    long long ntiles = 1;          // the most over the counts up to capacity
+    for (long long n : {1ll << 18, 1ll << 22, (long long)kMaxMarkers})
+        ntiles = std::max(ntiles, tiles_of(std::min<long long>(n, capacity)));
+    get((void**)&h->hist, (size_t)ntiles * p.most() * sizeof(int32_t));
+    get((void**)&h->total, (size_t)p.most() * sizeof(int32_t));
+    if (e == hipSuccess) {
+        e = grant_lds();
+        what = "LDS for the binning kernels";
+    }
     if (e != hipSuccess) {
         (void)hipGetLastError();
         tph_markers_destroy(h);
@@ -505,34 +945,32 @@ tph_status tph_markers_bin(tph_markers* h, int32_t kind, int32_t n, const double
         return TPH_ERR_INVALID;
     }
     const NodeGrid q = node_grid(h, kind);
-    const size_t ncell = (size_t)(h->nx + 1) * (h->ny + 1);
-    M_HIP(hipMemsetAsync(h->cstart, 0, ncell * sizeof(int32_t), h->st));
-    M_HIP(hipMemsetAsync(h->cend, 0, ncell * sizeof(int32_t), h->st));
-    h->kind = kind;
+    h->kind = -1;                  // no binning until all of its launches went through
     h->n = n;
     h->xm = xm;
     h->ym = ym;
-    h->sorted = 0;
-    if (n == 0) return TPH_OK;
-    hipLaunchKernelGGL(k_bin, dim3(blocks(n)), dim3(256), 0, h->st, q, h->nx, h->ny, n, xm, ym, h->keys[0],
-                       h->vals[0]);
+    const BinPlan p = bin_plan(h);
+    if (n > 0)
+        for (int pass = 0; pass < p.npass; ++pass) {
+            const int R = tile_rounds(n);
+            M_HIP(R == 1 ? launch_pass<1>(h, p, q, pass) : R == 4 ? launch_pass<4>(h, p, q, pass)
+                                                                  : launch_pass<16>(h, p, q, pass));
+        }
+    // one pass: from (keys[1], vals[0]) to vals[1]; two: from (keys[0], vals[1]) to vals[0]
+    const int ncell = (h->nx + 1) * (h->ny + 1);
+    int32_t* order = h->vals[p.npass & 1];
+    auto sort = [&](auto kernel, int nw, auto kin, const int32_t* vin) {
+        const size_t lds = (sizeof(int) + nw * sizeof(uint16_t)) << p.shift;
+        hipLaunchKernelGGL(kernel, dim3(p.buckets), dim3(nw * 64), lds, h->st, kin, vin, n, p.shift, ncell, h->total,
+                           h->cstart, order);
+    };
+    // four waves hold a bucket of up to 5120 markers, eight one of 10240
+    if (p.npass == 2) sort(k_cell_sort<8, uint32_t>, 8, (const uint32_t*)h->keys[0], h->vals[1]);
+    else if (n / p.buckets <= 4096) sort(k_cell_sort<4, uint16_t>, 4, (const uint16_t*)h->keys[1], h->vals[0]);
+    else sort(k_cell_sort<8, uint16_t>, 8, (const uint16_t*)h->keys[1], h->vals[0]);
     M_HIP(hipGetLastError());
-    const int ntiles = (n + kTile - 1) / kTile;
-    const long long len = (long long)ntiles * 256;
-    const int nchunks = (int)((len + kChunk - 1) / kChunk);
-    int cur = 0;
-    for (int shift = 0; shift < key_bits(h); shift += 8) {
-        hipLaunchKernelGGL(k_digit_count, dim3(ntiles), dim3(256), 0, h->st, h->keys[cur], n, ntiles, shift, h->hist);
-        hipLaunchKernelGGL(k_scan_chunks, dim3(nchunks), dim3(256), 0, h->st, h->hist, len, h->chunk);
-        hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(256), 0, h->st, h->chunk, nchunks);
-        hipLaunchKernelGGL(k_digit_scatter, dim3(ntiles), dim3(256), 0, h->st, h->keys[cur], h->vals[cur], n, ntiles,
-                           shift, h->hist, h->chunk, h->keys[1 - cur], h->vals[1 - cur]);
-        M_HIP(hipGetLastError());
-        cur = 1 - cur;
-    }
-    h->sorted = cur;
-    hipLaunchKernelGGL(k_ranges, dim3(blocks(n)), dim3(256), 0, h->st, n, h->keys[h->sorted], h->cstart, h->cend);
-    M_HIP(hipGetLastError());
+    h->order = order;
+    h->kind = kind;
     return TPH_OK;
 }
 
@@ -547,12 +985,23 @@ tph_status tph_markers_to_grid(tph_markers* h, const double* phi_m, double fill,
         return TPH_ERR_INVALID;
     }
     const NodeGrid q = node_grid(h, h->kind);
-    const int ncell = (h->nx + 1) * (h->ny + 1);
-    hipLaunchKernelGGL(k_cell_partials, dim3(blocks(ncell)), dim3(256), 0, h->st, q, h->nx, h->ny, h->cstart, h->cend,
-                       h->vals[h->sorted], h->xm, h->ym, phi_m, h->partial);
-    M_HIP(hipGetLastError());
-    const dim3 grid_((unsigned)((q.jmax - q.jmin + 1 + 255) / 256), (unsigned)(q.imax - q.imin + 1));
-    hipLaunchKernelGGL(k_nodes, grid_, dim3(256), 0, h->st, q, h->nx, h->ny, h->partial, fill, grid);
+    if (h->n == 0) {
+        const dim3 g((unsigned)((q.jmax - q.jmin + 1 + 255) / 256), (unsigned)(q.imax - q.imin + 1));
+        hipLaunchKernelGGL(k_fill_nodes, g, dim3(256), 0, h->st, q, fill, grid);
+        M_HIP(hipGetLastError());
+        return TPH_OK;
+    }
+    const double ncell = (double)(h->nx + 1) * (h->ny + 1);
+    const int R = ncell <= kRowCells ? 1 : 2, rows = kNodeWaves * R - 1;
+    const dim3 g((unsigned)((h->nx + 1 + 62) / 63), (unsigned)((h->ny + 1 + rows - 1) / rows));
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, g, dim3(kNodeWaves * 64), 0, h->st, q, h->nx, h->ny, h->cstart, h->order, h->xm,
+                           h->ym, phi_m, fill, grid);
+    };
+    // markers of 16 cells, with three deviations of a random placement; longer runs go in pieces of 320
+    const double run = 16.0 * h->n / ncell, most = run + 3.0 * std::sqrt(run);
+    if (R == 1) launch(most <= 128 ? k_nodes<1, 2> : most <= 192 ? k_nodes<1, 3> : most <= 256 ? k_nodes<1, 4> : k_nodes<1, 5>);
+    else launch(most <= 128 ? k_nodes<2, 2> : most <= 192 ? k_nodes<2, 3> : most <= 256 ? k_nodes<2, 4> : k_nodes<2, 5>);
     M_HIP(hipGetLastError());
     return TPH_OK;
 }
