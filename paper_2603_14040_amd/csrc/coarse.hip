@@ -29,87 +29,193 @@ __device__ __forceinline__ void unknown_to_node(const Geom& g, int m, int& comp,
     }
 }
 
-// Add coef * field(ci, cj) of an L row into row m of M = -L, resolving walls
-// (dropped) and ghosts (mirrored onto the adjacent unknown).
-__device__ __forceinline__ void add_ref(const Geom& g, double* row, int comp, int ci, int cj, double coef) {
+// Column of coef * field(ci, cj) in a row of M = -L, walls dropped (-1) and ghosts mirrored onto the
+// adjacent unknown (coef with them).
+__device__ __forceinline__ int column_of(const Geom& g, int comp, int ci, int cj, double& coef) {
     const int nvx = g.ny * (g.nx - 1);
     if (comp == 0) {
-        if (cj <= 0 || cj >= g.nx) return;
+        if (cj <= 0 || cj >= g.nx) return -1;
         if (ci == 0) { ci = 1; coef *= g.mir[2]; }
         else if (ci == g.ny + 1) { ci = g.ny; coef *= g.mir[3]; }
-        row[(ci - 1) * (g.nx - 1) + (cj - 1)] -= coef;
-    } else {
-        if (ci <= 0 || ci >= g.ny) return;
-        if (cj == 0) { cj = 1; coef *= g.mir[0]; }
-        else if (cj == g.nx + 1) { cj = g.nx; coef *= g.mir[1]; }
-        row[nvx + (ci - 1) * g.nx + (cj - 1)] -= coef;
+        return (ci - 1) * (g.nx - 1) + (cj - 1);
     }
+    if (ci <= 0 || ci >= g.ny) return -1;
+    if (cj == 0) { cj = 1; coef *= g.mir[0]; }
+    else if (cj == g.nx + 1) { cj = g.nx; coef *= g.mir[1]; }
+    return nvx + (ci - 1) * g.nx + (cj - 1);
 }
 
-__global__ void k_coarse_assemble(Geom g, const double* __restrict__ eb, const double* __restrict__ ep,
-                                  double* __restrict__ M, int n) {
-    const int m = blockIdx.x * blockDim.x + threadIdx.x;
-    if (m >= n) return;
-    double* row = M + (size_t)m * n;
-    for (int q = 0; q < n; ++q) row[q] = 0.0;
+// One workgroup per row: every lane knows the row's nine entries and writes the columns it comes to,
+// zeros and sums (a mirrored ghost meets an entry of its own), once and in whole lines.  A thread per row
+// that cleared it and added the entries in memory took 15 us at 112 unknowns and 49 us at 420.
+__global__ __launch_bounds__(64) void k_coarse_assemble(Geom g, const double* __restrict__ eb,
+                                                        const double* __restrict__ ep, double* __restrict__ M, int n) {
+    const int m = blockIdx.x;
     int comp, i, j;
     unknown_to_node(g, m, comp, i, j);
     const int P = g.pitch;
     const int c = i * P + j;
     const double idx2 = g.idx2, idy2 = g.idy2, idxy = 1.0 / (g.dx * g.dy);
+    int at[9];
+    double v[9];
+    int k = 0;
+    auto add = [&](int cp, int ci, int cj, double coef) {
+        at[k] = column_of(g, cp, ci, cj, coef);
+        v[k++] = coef;
+    };
     if (comp == 0) {
         const double er = ep[c + 1], el = ep[c], bt = eb[c], bb = eb[c - P];
-        add_ref(g, row, 0, i, j + 1, 2 * er * idx2);
-        add_ref(g, row, 0, i, j, -2 * (er + el) * idx2 - (bt + bb) * idy2);
-        add_ref(g, row, 0, i, j - 1, 2 * el * idx2);
-        add_ref(g, row, 0, i + 1, j, bt * idy2);
-        add_ref(g, row, 0, i - 1, j, bb * idy2);
-        add_ref(g, row, 1, i, j + 1, bt * idxy);
-        add_ref(g, row, 1, i, j, -bt * idxy);
-        add_ref(g, row, 1, i - 1, j + 1, -bb * idxy);
-        add_ref(g, row, 1, i - 1, j, bb * idxy);
+        add(0, i, j + 1, 2 * er * idx2);
+        add(0, i, j, -2 * (er + el) * idx2 - (bt + bb) * idy2);
+        add(0, i, j - 1, 2 * el * idx2);
+        add(0, i + 1, j, bt * idy2);
+        add(0, i - 1, j, bb * idy2);
+        add(1, i, j + 1, bt * idxy);
+        add(1, i, j, -bt * idxy);
+        add(1, i - 1, j + 1, -bb * idxy);
+        add(1, i - 1, j, bb * idxy);
     } else {
         const double et = ep[c + P], eb_ = ep[c], br = eb[c], bl = eb[c - 1];
-        add_ref(g, row, 1, i + 1, j, 2 * et * idy2);
-        add_ref(g, row, 1, i, j, -2 * (et + eb_) * idy2 - (br + bl) * idx2);
-        add_ref(g, row, 1, i - 1, j, 2 * eb_ * idy2);
-        add_ref(g, row, 1, i, j + 1, br * idx2);
-        add_ref(g, row, 1, i, j - 1, bl * idx2);
-        add_ref(g, row, 0, i + 1, j, br * idxy);
-        add_ref(g, row, 0, i, j, -br * idxy);
-        add_ref(g, row, 0, i + 1, j - 1, -bl * idxy);
-        add_ref(g, row, 0, i, j - 1, bl * idxy);
+        add(1, i + 1, j, 2 * et * idy2);
+        add(1, i, j, -2 * (et + eb_) * idy2 - (br + bl) * idx2);
+        add(1, i - 1, j, 2 * eb_ * idy2);
+        add(1, i, j + 1, br * idx2);
+        add(1, i, j - 1, bl * idx2);
+        add(0, i + 1, j, br * idxy);
+        add(0, i, j, -br * idxy);
+        add(0, i + 1, j - 1, -bl * idxy);
+        add(0, i, j - 1, bl * idxy);
+    }
+    double* row = M + (size_t)m * n;
+    for (int q = threadIdx.x; q < n; q += 64) {
+        double sum = 0.0;
+#pragma unroll
+        for (int t = 0; t < 9; ++t) sum = at[t] == q ? sum - v[t] : sum;
+        row[q] = sum;
     }
 }
 
-// In-place Gauss-Jordan inverse of an SPD matrix (no pivoting needed) in
-// memory, one step k per pair of launches over the whole device: the pivot
-// launch copies row k (scaled by 1 / M[k][k]) and column k into separate
-// vectors, so the elimination launch can overwrite both while every row
-// reads the values of the previous step.
-__global__ __launch_bounds__(256) void k_gj_pivot(const double* __restrict__ M, int n, int k,
-                                                  double* __restrict__ prow, double* __restrict__ pcol) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n) return;
-    const double rd = 1.0 / M[(size_t)k * n + k];
-    prow[t] = t == k ? rd : M[(size_t)k * n + t] * rd;
-    pcol[t] = M[(size_t)t * n + k];
+// In-place Gauss-Jordan inverse of an SPD matrix (no pivoting needed), kPanel steps per pair of launches.
+// Step k scales row k by 1 / M[k][k] and takes M[i][k] times it from every other row; an entry (i, j) needs
+// of a step only f = M[i][k] and p = M[k][j] / M[k][k] as they are then.
+//   k_gj_panel:  these factors for the panel's steps, F[s][i] and P[s][j].  A workgroup takes the panel's
+//                rows and columns and 32 further rows (for F) or columns (for P), and steps through those
+//                alone: entries in registers, row and column s published through LDS, one barrier a step.
+//   k_gj_update: every entry of a 32 x 32 tile through all the steps, the factors in LDS.
+// Each entry sees the operations of the plain algorithm in the same order.  Bound by the chain of n
+// pivots, about 0.5 us each (publish, barrier, division, update); a pair of launches per pivot took 4.8 us.
+// n = 212: 1030 us, now 213; n = 112: 278 us by one workgroup, now 114.
+constexpr int kPanel = 32;
+
+// SIDE 0: rows [k0, k0 + 32) and [t0, t0 + 32) of the panel's columns; 1: the transpose
+template <int SIDE>
+__device__ __forceinline__ void gj_panel(const double* __restrict__ M, int n, int k0, int t0,
+                                         double* __restrict__ out, double (*prow)[2 * kPanel],
+                                         double (*pcol)[2 * kPanel], double (*kept)[kPanel]) {
+    constexpr int NC = SIDE == 0 ? kPanel / 4 : 2 * kPanel / 4;        // threads across: 4 columns each, 2 rows
+    const int r0 = (threadIdx.x / NC) * 2, c0 = (threadIdx.x % NC) * 4;
+    // position relative to the panel: 0 .. 31 within, others are further rows or columns (or the panel's own again)
+    int gr[2], gc[4];
+#pragma unroll
+    for (int r = 0; r < 2; ++r) gr[r] = r0 + r < kPanel ? r0 + r : t0 + r0 + r - kPanel - k0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) gc[c] = c0 + c < kPanel ? c0 + c : t0 + c0 + c - kPanel - k0;
+    double a[2][4];
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int i = k0 + gr[r], j = k0 + gc[c];
+            a[r][c] = i < n && j < n ? M[(size_t)i * n + j] : 0.0;
+        }
+    const int steps = min(kPanel, n - k0);
+    for (int s4 = 0; s4 < steps; s4 += 4) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int s = s4 + q;
+            if (s >= steps) break;                                     // the same for every thread
+            double* pr = prow[q & 1];                                  // two buffers: one barrier a step
+            double* pc = pcol[q & 1];
+            if (r0 == s4 + (q & 2)) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) pr[c0 + c] = a[q & 1][c];
+            }
+            if (c0 == s4) {
+#pragma unroll
+                for (int r = 0; r < 2; ++r) pc[r0 + r] = a[r][q];
+            }
+            __syncthreads();
+            const double rd = 1.0 / pr[s];
+            double p[4], f[2];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) p[c] = gc[c] == s ? rd : pr[c0 + c] * rd;
+#pragma unroll
+            for (int r = 0; r < 2; ++r) f[r] = pc[r0 + r];
+            // kept until the end: the barrier would wait for a store to memory
+            if (SIDE == 0) {
+                if (c0 == 0 && r0 >= kPanel) {
+#pragma unroll
+                    for (int r = 0; r < 2; ++r) kept[s][r0 + r - kPanel] = f[r];
+                }
+            } else if (r0 == 0 && c0 >= kPanel) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) kept[s][c0 + c - kPanel] = p[c];
+            }
+#pragma unroll
+            for (int r = 0; r < 2; ++r)
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    a[r][c] = gr[r] == s ? p[c] : gc[c] == s ? -f[r] * rd : __builtin_fma(-f[r], p[c], a[r][c]);
+        }
+    }
+    __syncthreads();
+    for (int t = threadIdx.x; t < steps * kPanel; t += 256)
+        if (t0 + t % kPanel < n) out[(size_t)(t / kPanel) * n + t0 + t % kPanel] = kept[t / kPanel][t % kPanel];
 }
 
-__global__ __launch_bounds__(256) void k_gj_eliminate(double* __restrict__ M, int n, int k,
-                                                      const double* __restrict__ prow,
-                                                      const double* __restrict__ pcol) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    const int i = blockIdx.y;
-    if (j >= n) return;
-    double* ri = M + (size_t)i * n;
-    if (i == k) {
-        ri[j] = prow[j];
-        return;
+__global__ __launch_bounds__(256) void k_gj_panel(const double* __restrict__ M, int n, int k0,
+                                                  double* __restrict__ F, double* __restrict__ P) {
+    __shared__ double prow[2][2 * kPanel], pcol[2][2 * kPanel], kept[kPanel][kPanel];
+    const int t0 = (int)blockIdx.x * kPanel;
+    if (blockIdx.y == 0) gj_panel<0>(M, n, k0, t0, F, prow, pcol, kept);
+    else gj_panel<1>(M, n, k0, t0, P, prow, pcol, kept);
+}
+
+__global__ __launch_bounds__(256) void k_gj_update(double* __restrict__ M, int n, int k0, const double* __restrict__ F,
+                                                   const double* __restrict__ P) {
+    __shared__ double f[kPanel][kPanel], p[kPanel][kPanel];
+    const int i0 = (int)blockIdx.y * kPanel, j0 = (int)blockIdx.x * kPanel;
+    const int steps = min(kPanel, n - k0);
+    for (int t = threadIdx.x; t < kPanel * kPanel; t += 256) {         // steps past the last: factors of zero, no change
+        const int s = t / kPanel, l = t % kPanel;
+        f[s][l] = s < steps && i0 + l < n ? F[(size_t)s * n + i0 + l] : 0.0;
+        p[s][l] = s < steps && j0 + l < n ? P[(size_t)s * n + j0 + l] : 0.0;
     }
-    const double f = pcol[i];
-    if (j != k) ri[j] -= f * prow[j];
-    else ri[j] = -f * prow[k];
+    const int l = threadIdx.x % kPanel, r0 = threadIdx.x / kPanel;     // column, first of the rows r0 + 8 q
+    const int j = j0 + l;
+    double a[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) a[q] = i0 + r0 + 8 * q < n && j < n ? M[(size_t)(i0 + r0 + 8 * q) * n + j] : 0.0;
+    __syncthreads();
+    if (i0 != k0 && j0 != k0) {                                        // k0 is a multiple of the tile's size
+#pragma unroll 8
+        for (int s = 0; s < kPanel; ++s) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) a[q] = __builtin_fma(-f[s][r0 + 8 * q], p[s][l], a[q]);
+        }
+    } else {
+#pragma unroll 4
+        for (int s = 0; s < kPanel; ++s) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const double fs = f[s][r0 + 8 * q], ps = p[s][l];
+                a[q] = i0 + r0 + 8 * q == k0 + s ? ps : j == k0 + s ? -fs * ps : __builtin_fma(-fs, ps, a[q]);
+            }
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        if (i0 + r0 + 8 * q < n && j < n) M[(size_t)(i0 + r0 + 8 * q) * n + j] = a[q];
 }
 
 // Gauss-Jordan inversion of a small SPD matrix (n <= kGJLds) by one
@@ -118,8 +224,9 @@ __global__ __launch_bounds__(256) void k_gj_eliminate(double* __restrict__ M, in
 // consecutive entries.  Each step k copies the old row k and column k to
 // LDS, then every thread updates its own entries (the same operations as
 // the device-wide form: row k scaled by 1 / M[k][k], the others reduced by
-// the scaled row), two barriers per step.  Blocks of a batched launch each
-// invert their own matrix (mats[blockIdx.x], sizes ns[blockIdx.x]).
+// the scaled row), two barriers per step.  Blocks each invert their own
+// matrix (mats[blockIdx.x], sizes ns[blockIdx.x]): one launch for a batch, 278 us
+// at n = 112 however many there are up to the number of CUs.
 constexpr int kGJThreads = 1024;
 constexpr int kGJRun = 20;   // max over n <= 136 of ceil(n / floor(1024 / n))
 static_assert(kGJThreads >= kGJLds, "one row per thread at least");
@@ -211,7 +318,7 @@ __global__ __launch_bounds__(256) void k_coarse_solve(Geom g, const double* __re
 
 hipError_t launch_coarse_assemble(const Geom& g, const double* eb, const double* ep, double* M, hipStream_t st) {
     const int n = coarse_unknowns(g);
-    hipLaunchKernelGGL(k_coarse_assemble, dim3((n + 127) / 128), dim3(128), 0, st, g, eb, ep, M, n);
+    hipLaunchKernelGGL(k_coarse_assemble, dim3(n), dim3(64), 0, st, g, eb, ep, M, n);
     return hipGetLastError();
 }
 
@@ -241,18 +348,16 @@ hipError_t launch_gauss_jordan_batched(double* const* mats, const int* ns, int c
     return hipGetLastError();
 }
 
-hipError_t launch_gauss_jordan(double* M, int n, hipStream_t st, double** table, double* work) {
-    if (n <= kGJLds && table) {
-        // table: device scratch of one pointer and one int (owned by the caller)
-        return launch_gauss_jordan_batched(table, (const int*)(table + 1), 1, n, st);
-    }
+size_t gauss_jordan_work(int n) { return 2 * (size_t)kPanel * n; }
+
+hipError_t launch_gauss_jordan(double* M, int n, hipStream_t st, double* work) {
     if (!work) return hipErrorInvalidValue;
-    double* prow = work;
-    double* pcol = work + n;
-    const dim3 g1((n + 255) / 256), g2((n + 255) / 256, n);
-    for (int k = 0; k < n; ++k) {
-        hipLaunchKernelGGL(k_gj_pivot, g1, dim3(256), 0, st, M, n, k, prow, pcol);
-        hipLaunchKernelGGL(k_gj_eliminate, g2, dim3(256), 0, st, M, n, k, prow, pcol);
+    double* F = work;
+    double* P = work + (size_t)kPanel * n;
+    const unsigned tiles = (unsigned)((n + kPanel - 1) / kPanel);
+    for (int k0 = 0; k0 < n; k0 += kPanel) {
+        hipLaunchKernelGGL(k_gj_panel, dim3(tiles, 2), dim3(256), 0, st, M, n, k0, F, P);
+        hipLaunchKernelGGL(k_gj_update, dim3(tiles, tiles), dim3(256), 0, st, M, n, k0, F, P);
     }
     return hipGetLastError();
 }

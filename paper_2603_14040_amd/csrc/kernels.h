@@ -109,12 +109,11 @@ int coarse_unknowns(const Geom& g);
 hipError_t launch_coarse_assemble(const Geom& g, const double* eb, const double* ep, double* M,
                                   hipStream_t st);
 // In-place inverse of the n x n SPD matrix M (row-major) by Gauss-Jordan
-// elimination.  n <= kGJLds: one workgroup in LDS, which needs `table`:
-// device memory holding {M, (int)n} as written by the caller (a pointer
-// followed by an int).  Larger n: 2 n launches over the device with `work`
-// = 2 n doubles of device scratch.
+// elimination, two launches per 32 steps; work: gauss_jordan_work(n) doubles
+// of device scratch
+size_t gauss_jordan_work(int n);
+hipError_t launch_gauss_jordan(double* M, int n, hipStream_t st, double* work);
 constexpr int kGJLds = 136;    // largest n inverted by one workgroup (registers, 2 n doubles of LDS)
-hipError_t launch_gauss_jordan(double* M, int n, hipStream_t st, double** table, double* work);
 // one workgroup per matrix: mats[i] (device array of device pointers), sizes
 // ns[i] <= kGJLds, nmax = max ns[i]
 hipError_t launch_gauss_jordan_batched(double* const* mats, const int* ns, int count, int nmax, hipStream_t st);
