@@ -137,24 +137,45 @@ hipError_t launch_ras_tile(const Geom& g, int tile, int si, int sj, int inner, b
 
 // ----------------------------------------------------------------- krylov.hip
 int flat_blocks(size_t n);
+// Kernels of a second projection that are launched before the host knows whether it is needed: norm2 and
+// before are |w|^2 after the first and before it, in device memory.  With norm2 null there is no question.
+struct Again {
+    const double* norm2;
+    const double* before;
+    __device__ bool asked() const { return norm2 != nullptr; }
+    __device__ bool needed() const { return *norm2 < 0.5 * *before; }
+};
 // partial[i * nblk + b] = sum over block b of V_i . w (any nv); when norm_slot >= 0
 // also partial[norm_slot * nblk + b] = block sums of w . w
 hipError_t launch_multidot(const double* V0, size_t vstride, int nv, const double* w, size_t n,
-                           double* partial, int nblk, hipStream_t st, int norm_slot = -1);
+                           double* partial, int nblk, hipStream_t st, int norm_slot = -1, Again again = {});
 // w -= sum_i h[i] V_i (h in device memory), partial[b] = block sums of the new w . w
 hipError_t launch_axpy_norm(double* w, const double* V0, size_t vstride, int nv, const double* h, size_t n,
-                            double* partial, int nblk, hipStream_t st);
+                            double* partial, int nblk, hipStream_t st, Again again = {});
+// the same with h the row sums of rows.partial (k >= nv rows of nblk), written to out and host (mapped
+// memory) as well; nblk <= sum_blocks_max(), partial another part of memory
+struct RowSums {
+    const double* partial;
+    double* out;
+    double* host;
+    int nblk, k;
+};
+int sum_blocks_max();
+hipError_t launch_axpy_norm_sums(double* w, const double* V0, size_t vstride, int nv, const RowSums& rows, size_t n,
+                                 double* partial, hipStream_t st, Again again = {});
 // out[i] = sum_b partial[i * nblk + b], i < k  (fixed order: deterministic)
 // row sums of partial (k rows of nblk) into out; also into host_out (a device
 // pointer to mapped coherent host memory) when it is not null.  With host_seq
 // not null, the kernel then writes seq to *host_seq (mapped host memory) after a
 // system-scope fence, so a host that sees seq there also sees every value
-// written to host memory by this and earlier kernels.
+// written to host memory by this and earlier kernels.  Where a second projection
+// was not needed, every row's sum is the norm that it would have replaced.
 hipError_t launch_reduce_rows(const double* partial, int nblk, int k, double* out, hipStream_t st,
-                              double* host_out = nullptr, unsigned* host_seq = nullptr, unsigned seq = 0);
-// dst = src / sqrt(*nrm2)
+                              double* host_out = nullptr, unsigned* host_seq = nullptr, unsigned seq = 0,
+                              Again again = {});
+// dst = src / sqrt(*nrm2); not where a second projection is needed
 hipError_t launch_scale_by_rnorm(double* dst, const double* src, size_t n, const double* nrm2,
-                                 hipStream_t st);
+                                 hipStream_t st, Again again = {});
 // x += sum_j y[j] Z_j (y on the host, k <= kMaxRestart; n and zstride even, 16-byte aligned)
 hipError_t launch_update_x(double* x, const double* Z0, size_t zstride, int k, const double* y,
                            size_t n, hipStream_t st);

@@ -42,8 +42,9 @@ typedef double D2 __attribute__((ext_vector_type(2)));
 template <int NV>
 __global__ __launch_bounds__(256) void k_multidot(const double* __restrict__ V0, size_t vstride, int nv,
                                                  const double* __restrict__ w, size_t n,
-                                                 double* __restrict__ partial, int nblk, int norm_slot) {
+                                                 double* __restrict__ partial, int nblk, int norm_slot, Again again) {
     __shared__ double part[4 * NV];
+    if (again.asked() && !again.needed()) return;
     const int v0 = blockIdx.y * NV;
     const double* V[NV];
 #pragma unroll
@@ -80,11 +81,44 @@ __global__ __launch_bounds__(256) void k_multidot(const double* __restrict__ V0,
 
 // w -= sum_i h[i] V_i for any number of vectors, with the block sums of the new
 // w . w, in one pass over w (8 vectors' loads in flight at a time; a launch per 8
-// vectors re-read w and paid 5 us each on short vectors)
+// vectors re-read w and paid 5 us each on short vectors).
+// SUMS: h is not there yet.  Every workgroup adds up the rows of block sums that it comes from by
+// itself, a row per wave and in k_reduce_rows' order, and the first one writes them out: for the few blocks
+// of a small grid (at most kSumBlocks) that takes 1 us where a launch for it took 4.
+constexpr int kSumBlocks = 128;
+template <bool SUMS>
 __global__ __launch_bounds__(256) void k_axpy_norm(double* __restrict__ w, const double* __restrict__ V0,
                                                   size_t vstride, int nv, const double* __restrict__ h, size_t n,
-                                                  double* __restrict__ partial) {
+                                                  double* __restrict__ partial, RowSums rows, Again again) {
     __shared__ double part[4];
+    __shared__ double hs[kMaxRestart + 2];
+    if (again.asked() && !again.needed()) return;
+    if (SUMS) {
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        constexpr int U = 4, Q = kSumBlocks / 64;        // rows in flight per wave, entries of a lane
+        for (int r0 = wave; r0 < rows.k; r0 += 4 * U) {
+            double v[U][Q];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    const int r = min(r0 + 4 * u, rows.k - 1), b = q * 64 + lane;
+                    v[u][q] = b < rows.nblk ? rows.partial[(size_t)r * rows.nblk + b] : 0.0;
+                }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                double t = 0.0;
+#pragma unroll
+                for (int q = 0; q < Q; ++q) t += wave_sum(0.0 + v[u][q]);
+                if (lane == 0 && r0 + 4 * u < rows.k) hs[r0 + 4 * u] = t;
+            }
+        }
+        __syncthreads();
+        if (blockIdx.x == 0 && (int)threadIdx.x < rows.k) {
+            rows.out[threadIdx.x] = hs[threadIdx.x];
+            rows.host[threadIdx.x] = hs[threadIdx.x];
+        }
+    }
     double acc[1] = {0.0};
     const size_t step = (size_t)gridDim.x * 256;
     constexpr int U = 4;
@@ -105,7 +139,7 @@ __global__ __launch_bounds__(256) void k_axpy_norm(double* __restrict__ w, const
                     y[u][v] = in[u] && v0 + v < nv ? V0[(v0 + v) * vstride + t0 + u * step] : 0.0;
 #pragma unroll
             for (int v = 0; v < kNV; ++v) {
-                const double hv = v0 + v < nv ? h[v0 + v] : 0.0;
+                const double hv = v0 + v < nv ? (SUMS ? hs[v0 + v] : h[v0 + v]) : 0.0;
 #pragma unroll
                 for (int u = 0; u < U; ++u) x[u] -= hv * y[u][v];
             }
@@ -129,9 +163,10 @@ constexpr int kRowThreads = 256;
 constexpr int kRowGroups = 4;
 __global__ __launch_bounds__(kRowThreads * kRowGroups) void k_reduce_rows(
     const double* __restrict__ partial, int nblk, int k, double* __restrict__ out, double* __restrict__ host_out,
-    unsigned* __restrict__ host_seq, unsigned seq) {
+    unsigned* __restrict__ host_seq, unsigned seq, Again again) {
     __shared__ double part[kRowGroups][kRowThreads / 64];
     const int grp = threadIdx.x / kRowThreads, tid = threadIdx.x % kRowThreads;
+    const bool left_out = again.asked() && !again.needed();
     for (int r0 = 0; r0 < k; r0 += kRowGroups) {
         const int r = r0 + grp;
         double s = 0.0;
@@ -153,6 +188,7 @@ __global__ __launch_bounds__(kRowThreads * kRowGroups) void k_reduce_rows(
         if (tid == 0 && r < k) {
             double t = 0.0;
             for (int q = 0; q < kRowThreads / 64; ++q) t += part[grp][q];
+            if (left_out) t = *again.norm2;       // the norm that stays
             out[r] = t;
             if (host_out) host_out[r] = t;
         }
@@ -166,7 +202,8 @@ __global__ __launch_bounds__(kRowThreads * kRowGroups) void k_reduce_rows(
 }
 
 __global__ __launch_bounds__(256) void k_scale_rnorm(double* __restrict__ dst, const double* __restrict__ src,
-                                                    size_t n, const double* __restrict__ nrm2) {
+                                                    size_t n, const double* __restrict__ nrm2, Again again) {
+    if (again.asked() && again.needed()) return;      // not the last pass
     const double r = 1.0 / sqrt(nrm2[0]);
     for (size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x; t < n; t += (size_t)gridDim.x * blockDim.x)
         dst[t] = src[t] * r;
@@ -305,12 +342,12 @@ __global__ __launch_bounds__(256) void k_p_shift(Geom g, double* __restrict__ p,
 }  // namespace
 
 hipError_t launch_multidot(const double* V0, size_t vstride, int nv, const double* w, size_t n, double* partial,
-                           int nblk, hipStream_t st, int norm_slot) {
+                           int nblk, hipStream_t st, int norm_slot, Again again) {
     const int rows = nv + (norm_slot >= 0 ? 1 : 0);
     // vectors per block: 8 once the blocks of one group fill the chip by
     // themselves (two per CU), fewer while they do not; nblk is n / 2048
     const int per = nblk >= 512 ? 8 : nblk >= 128 ? 4 : 1;
-#define TPH_DOT(NV)                                                                                                    hipLaunchKernelGGL((k_multidot<NV>), dim3(nblk, (rows + NV - 1) / NV), dim3(256), 0, st, V0, vstride, nv, w, n,                        partial, nblk, norm_slot)
+#define TPH_DOT(NV)                                                                                                    hipLaunchKernelGGL((k_multidot<NV>), dim3(nblk, (rows + NV - 1) / NV), dim3(256), 0, st, V0, vstride, nv, w, n,                        partial, nblk, norm_slot, again)
     if (per == 8) TPH_DOT(8);
     else if (per == 4) TPH_DOT(4);
     else TPH_DOT(1);
@@ -319,20 +356,33 @@ hipError_t launch_multidot(const double* V0, size_t vstride, int nv, const doubl
 }
 
 hipError_t launch_axpy_norm(double* w, const double* V0, size_t vstride, int nv, const double* h, size_t n,
-                            double* partial, int nblk, hipStream_t st) {
-    hipLaunchKernelGGL(k_axpy_norm, dim3(nblk), dim3(256), 0, st, w, V0, vstride, nv, h, n, partial);
+                            double* partial, int nblk, hipStream_t st, Again again) {
+    hipLaunchKernelGGL((k_axpy_norm<false>), dim3(nblk), dim3(256), 0, st, w, V0, vstride, nv, h, n, partial, RowSums{},
+                       again);
+    return hipGetLastError();
+}
+
+int sum_blocks_max() { return kSumBlocks; }
+
+hipError_t launch_axpy_norm_sums(double* w, const double* V0, size_t vstride, int nv, const RowSums& rows, size_t n,
+                                 double* partial, hipStream_t st, Again again) {
+    if (rows.nblk < 1 || rows.nblk > kSumBlocks || rows.k < nv || rows.k < 1 || rows.k > kMaxRestart + 2)
+        return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_axpy_norm<true>), dim3(rows.nblk), dim3(256), 0, st, w, V0, vstride, nv, nullptr, n, partial,
+                       rows, again);
     return hipGetLastError();
 }
 
 hipError_t launch_reduce_rows(const double* partial, int nblk, int k, double* out, hipStream_t st,
-                              double* host_out, unsigned* host_seq, unsigned seq) {
+                              double* host_out, unsigned* host_seq, unsigned seq, Again again) {
     hipLaunchKernelGGL(k_reduce_rows, dim3(1), dim3(kRowThreads * kRowGroups), 0, st, partial, nblk, k, out, host_out,
-                       host_seq, seq);
+                       host_seq, seq, again);
     return hipGetLastError();
 }
 
-hipError_t launch_scale_by_rnorm(double* dst, const double* src, size_t n, const double* nrm2, hipStream_t st) {
-    hipLaunchKernelGGL(k_scale_rnorm, dim3(flat_blocks(n)), dim3(256), 0, st, dst, src, n, nrm2);
+hipError_t launch_scale_by_rnorm(double* dst, const double* src, size_t n, const double* nrm2, hipStream_t st,
+                                 Again again) {
+    hipLaunchKernelGGL(k_scale_rnorm, dim3(flat_blocks(n)), dim3(256), 0, st, dst, src, n, nrm2, again);
     return hipGetLastError();
 }
 

@@ -56,7 +56,8 @@ void set_error(const std::string& m) { g_last_error = m; }
 constexpr int kSlotH1 = 0;                        // kMaxRestart + 1 entries
 constexpr int kSlotH2 = kSlotH1 + kMaxRestart + 1;
 constexpr int kSlotNrm = kSlotH2 + kMaxRestart + 1;
-constexpr int kSlotMisc = kSlotNrm + 1;           // 8 entries
+constexpr int kSlotNrm2 = kSlotNrm + 1;           // after a second projection
+constexpr int kSlotMisc = kSlotNrm2 + 1;          // 8 entries
 constexpr int kScalars = kSlotMisc + 8;
 
 struct LevelBuf {
@@ -722,10 +723,32 @@ tph_status precondition(tph_solver* s, double* vraw, double* zraw, bool energy, 
 // kernel also writes them into the mapped host mirror (no copy launch).  A
 // reduction with `signal` ends the values the host is about to read: it also
 // posts the next sequence number, which wait_signal() polls.
-tph_status reduce_to(tph_solver* s, int nblk, int k, int slot, bool to_host = false, bool signal = false) {
-    TPH_HIP(launch_reduce_rows(s->partial, nblk, k, s->dscal + slot, s->st, to_host ? s->hscal_dev + slot : nullptr,
-                               signal ? s->hseq_dev : nullptr, signal ? ++s->seq : 0u));
+tph_status reduce_to(tph_solver* s, int nblk, int k, int slot, bool to_host = false, bool signal = false,
+                     const double* partial = nullptr, Again again = {}) {
+    TPH_HIP(launch_reduce_rows(partial ? partial : s->partial, nblk, k, s->dscal + slot, s->st,
+                               to_host ? s->hscal_dev + slot : nullptr, signal ? s->hseq_dev : nullptr,
+                               signal ? ++s->seq : 0u, again));
     return TPH_OK;
+}
+
+// One Gram-Schmidt pass of FGMRES: w -= sum_i <V_i, w> V_i over the first nv vectors, the coefficients (and
+// |w|^2 behind them, with_norm) to `slot` and the host, |w|^2 of what is left to nslot, with a signal.  On grids
+// of few blocks the projection adds up the dot products itself.
+tph_status project_out(tph_solver* s, double* w, int nv, size_t n, int nblk, bool with_norm, int slot, int nslot,
+                       Again again) {
+    const int k = nv + (with_norm ? 1 : 0);
+    const double* V0 = s->V;
+    TPH_HIP(launch_multidot(V0, n, nv, w, n, s->partial, nblk, s->st, with_norm ? nv : -1, again));
+    double* norms = s->partial;
+    if (nblk <= sum_blocks_max()) {
+        norms += (size_t)k * nblk;               // the rows are still read
+        const RowSums rows{s->partial, s->dscal + slot, s->hscal_dev + slot, nblk, k};
+        TPH_HIP(launch_axpy_norm_sums(w, V0, n, nv, rows, n, norms, s->st, again));
+    } else {
+        TPH_TRY(reduce_to(s, nblk, k, slot, true, false, nullptr, again));
+        TPH_HIP(launch_axpy_norm(w, V0, n, nv, s->dscal + slot, n, s->partial, nblk, s->st, again));
+    }
+    return reduce_to(s, nblk, 1, nslot, true, true, norms, again);
 }
 
 // Wait until the last signalling reduction has posted its sequence number.
@@ -887,32 +910,44 @@ tph_status fgmres(tph_solver* s, double* braw, tph_info* info) {
         std::fill(gv.begin(), gv.end(), 0.0);
         gv[0] = beta;
         int jdone = 0;
+        bool expect_second = false;
         for (int j = 0; j < m; ++j) {
             // z_j = M^{-1} v_j and w = W^(1/2) A z_j (the apply fused into the last Uzawa step's exit)
             TPH_TRY(precondition(s, Vk(j), Zk(j), true, Vk(j + 1)));
             double* w = Vk(j + 1);
             // classical Gram-Schmidt with selective re-orthogonalisation: one
             // projection pass, and a second only when the norm drops below
-            // 1/sqrt(2) of its value before the projection (cancellation)
-            TPH_HIP(launch_multidot(Vk(0), n3, j + 1, w, n3, s->partial, nblk_flat, s->st, j + 1));
-            TPH_TRY(reduce_to(s, nblk_flat, j + 2, kSlotH1, true));  // h (j+1) and |w|^2 at kSlotH1 + j + 1
-            TPH_HIP(launch_axpy_norm(w, Vk(0), n3, j + 1, s->dscal + kSlotH1, n3, s->partial, nblk_flat, s->st));
-            TPH_TRY(reduce_to(s, nblk_flat, 1, kSlotNrm, true, true));
+            // 1/sqrt(2) of its value before the projection (cancellation).
+            // After a step that needed the second, the next one's is launched
+            // behind the first (its kernels see for themselves whether it is
+            // needed): the host waits once a step, not twice.  The new
+            // vector is scaled while the host works.
+            const Again again{s->dscal + kSlotNrm, s->dscal + kSlotH1 + j + 1};
+            TPH_TRY(project_out(s, w, j + 1, n3, nblk_flat, true, kSlotH1, kSlotNrm, {}));
+            if (expect_second) {
+                TPH_TRY(project_out(s, w, j + 1, n3, nblk_flat, false, kSlotH2, kSlotNrm2, again));
+                TPH_HIP(launch_scale_by_rnorm(w, w, n3, s->dscal + kSlotNrm2, s->st));
+            } else {
+                TPH_HIP(launch_scale_by_rnorm(w, w, n3, s->dscal + kSlotNrm, s->st, again));
+            }
             TPH_TRY(wait_signal(s));
             double* col = &H[(size_t)j * (m + 1)];
             for (int i = 0; i <= j; ++i) col[i] = s->hscal[kSlotH1 + i];
             const double w2_before = s->hscal[kSlotH1 + j + 1];
-            if (s->hscal[kSlotNrm] < 0.5 * w2_before) {
-                TPH_HIP(launch_multidot(Vk(0), n3, j + 1, w, n3, s->partial, nblk_flat, s->st));
-                TPH_TRY(reduce_to(s, nblk_flat, j + 1, kSlotH2, true));
-                TPH_HIP(launch_axpy_norm(w, Vk(0), n3, j + 1, s->dscal + kSlotH2, n3, s->partial, nblk_flat, s->st));
-                TPH_TRY(reduce_to(s, nblk_flat, 1, kSlotNrm, true, true));
-                TPH_TRY(wait_signal(s));
+            double w2 = s->hscal[kSlotNrm];
+            const bool second = w2 < 0.5 * w2_before;
+            if (second) {
+                if (!expect_second) {
+                    TPH_TRY(project_out(s, w, j + 1, n3, nblk_flat, false, kSlotH2, kSlotNrm2, {}));
+                    TPH_HIP(launch_scale_by_rnorm(w, w, n3, s->dscal + kSlotNrm2, s->st));
+                    TPH_TRY(wait_signal(s));
+                }
                 for (int i = 0; i <= j; ++i) col[i] += s->hscal[kSlotH2 + i];
+                w2 = s->hscal[kSlotNrm2];
                 ++s->reorth_count;
             }
-            TPH_HIP(launch_scale_by_rnorm(w, w, n3, s->dscal + kSlotNrm, s->st));
-            const double hn = std::sqrt(s->hscal[kSlotNrm]);
+            expect_second = second;
+            const double hn = std::sqrt(w2);
             col[j + 1] = hn;
             if (!std::isfinite(hn)) { set_error("non-finite value in the Krylov basis"); return TPH_ERR_NONFINITE; }
             for (int i = 0; i < j; ++i) {
