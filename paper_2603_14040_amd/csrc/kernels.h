@@ -92,6 +92,15 @@ struct CastList {
 };
 hipError_t launch_cast_list(const CastList& c, hipStream_t st);
 
+// Copies of up to five w x h fields between a caller's dense arrays and pitched ones, in one launch (pitches in entries)
+struct FieldCopies {
+    const double* src[5];
+    double* dst[5];
+    int count, w, h;
+    size_t spitch, dpitch;
+};
+hipError_t launch_copy_fields(const FieldCopies& c, hipStream_t st);
+
 // --------------------------------------------------------------- transfer.hip
 // coarse viscosities from fine ones (normalised bilinear gather; geometric = log-mean)
 hipError_t launch_restrict_eta(const Geom& gf, const Geom& gc, const double* ebf, const double* epf,

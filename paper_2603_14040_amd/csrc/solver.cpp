@@ -19,6 +19,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <initializer_list>
 #include <string>
 #include <vector>
 
@@ -814,26 +815,57 @@ tph_status rounding_floor(tph_solver* s, double* xraw, double* braw, double bnor
 // solve keeps going (slow convergence is not a floor).
 constexpr double kFloorMargin = 100.0;
 
-tph_status copy_in(tph_solver* s, const Geom& g, double* base, const double* user) {
-    const size_t w = (size_t)(g.nx + 2) * sizeof(double);
-    TPH_HIP(hipMemcpy2DAsync(base, (size_t)g.pitch * sizeof(double), user, w, w, g.ny + 2, hipMemcpyDeviceToDevice,
-                             s->st));
+// the caller's dense arrays into pitched fields and back, up to five at once; a null array is left out
+struct FieldIn { double* base; const double* user; };
+struct FieldOut { double* user; const double* base; };
+
+tph_status copy_in(tph_solver* s, const Geom& g, std::initializer_list<FieldIn> fields) {
+    FieldCopies c{};
+    c.w = g.nx + 2;
+    c.h = g.ny + 2;
+    c.spitch = (size_t)c.w;
+    c.dpitch = (size_t)g.pitch;
+    for (const FieldIn& f : fields) {
+        if (!f.user) continue;
+        c.src[c.count] = f.user;
+        c.dst[c.count++] = f.base;
+    }
+    TPH_HIP(launch_copy_fields(c, s->st));
     return TPH_OK;
 }
 
-tph_status copy_out(tph_solver* s, const Geom& g, double* user, const double* base) {
-    const size_t w = (size_t)(g.nx + 2) * sizeof(double);
-    TPH_HIP(hipMemcpy2DAsync(user, w, base, (size_t)g.pitch * sizeof(double), w, g.ny + 2, hipMemcpyDeviceToDevice,
-                             s->st));
+tph_status copy_out(tph_solver* s, const Geom& g, std::initializer_list<FieldOut> fields) {
+    FieldCopies c{};
+    c.w = g.nx + 2;
+    c.h = g.ny + 2;
+    c.spitch = (size_t)g.pitch;
+    c.dpitch = (size_t)c.w;
+    const uintptr_t bytes = (uintptr_t)c.w * c.h * sizeof(double);
+    for (const FieldOut& f : fields) {
+        if (!f.user) continue;
+        bool apart = true;                       // arrays that overlap are written one after the other
+        for (int k = 0; k < c.count; ++k) {
+            const uintptr_t x = (uintptr_t)c.dst[k], y = (uintptr_t)f.user;
+            apart = apart && (x + bytes <= y || y + bytes <= x);
+        }
+        if (!apart) {
+            TPH_HIP(launch_copy_fields(c, s->st));
+            c.count = 0;
+        }
+        c.src[c.count] = f.base;
+        c.dst[c.count++] = f.user;
+    }
+    TPH_HIP(launch_copy_fields(c, s->st));
     return TPH_OK;
 }
 
 tph_status load_solution(tph_solver* s, double* raw, const double* vx, const double* vy, const double* p) {
     const Geom& g = s->lev[0].g;
     Vec3 x = vec3(s, raw);
-    if (vx) TPH_TRY(copy_in(s, g, x.vx(), vx)); else TPH_HIP(hipMemsetAsync(raw, 0, s->F * sizeof(double), s->st));
-    if (vy) TPH_TRY(copy_in(s, g, x.vy(), vy)); else TPH_HIP(hipMemsetAsync(raw + s->F, 0, s->F * sizeof(double), s->st));
-    if (p) TPH_TRY(copy_in(s, g, x.p(), p)); else TPH_HIP(hipMemsetAsync(raw + 2 * s->F, 0, s->F * sizeof(double), s->st));
+    if (!vx) TPH_HIP(hipMemsetAsync(raw, 0, s->F * sizeof(double), s->st));
+    if (!vy) TPH_HIP(hipMemsetAsync(raw + s->F, 0, s->F * sizeof(double), s->st));
+    if (!p) TPH_HIP(hipMemsetAsync(raw + 2 * s->F, 0, s->F * sizeof(double), s->st));
+    TPH_TRY(copy_in(s, g, {{x.vx(), vx}, {x.vy(), vy}, {x.p(), p}}));
     TPH_HIP(launch_fill_bc<double>(g, x.vx(), x.vy(), s->st));
     return TPH_OK;
 }
@@ -841,9 +873,7 @@ tph_status load_solution(tph_solver* s, double* raw, const double* vx, const dou
 tph_status store_solution(tph_solver* s, const double* raw, double* vx, double* vy, double* p) {
     const Geom& g = s->lev[0].g;
     Vec3 x = vec3(s, (double*)raw);
-    if (vx) TPH_TRY(copy_out(s, g, vx, x.vx()));
-    if (vy) TPH_TRY(copy_out(s, g, vy, x.vy()));
-    if (p) TPH_TRY(copy_out(s, g, p, x.p()));
+    TPH_TRY(copy_out(s, g, {{vx, x.vx()}, {vy, x.vy()}, {p, x.p()}}));
     return TPH_OK;
 }
 
@@ -1703,13 +1733,10 @@ tph_status setup_enqueue(tph_solver* s, const double* eta_b, const double* eta_p
     s->ready = false;
     const Geom& g0 = s->lev[0].g;
     TPH_HIP(hipEventRecord(s->ev0, s->st));
-    TPH_TRY(copy_in(s, g0, s->lev[0].eb64, eta_b));
-    TPH_TRY(copy_in(s, g0, s->lev[0].ep64, eta_p));
-    TPH_TRY(copy_in(s, g0, s->rho, rho_b));
     s->has_fx = fx_extra != nullptr;
     s->has_fy = fy_extra != nullptr;
-    if (fx_extra) TPH_TRY(copy_in(s, g0, s->fxe, fx_extra));
-    if (fy_extra) TPH_TRY(copy_in(s, g0, s->fye, fy_extra));
+    TPH_TRY(copy_in(s, g0, {{s->lev[0].eb64, eta_b}, {s->lev[0].ep64, eta_p}, {s->rho, rho_b}, {s->fxe, fx_extra},
+                            {s->fye, fy_extra}}));
     int nblk = 0;
     TPH_HIP(launch_check_coeffs(g0, s->lev[0].eb64, s->lev[0].ep64, s->rho, s->has_fx ? s->fxe : nullptr,
                                 s->has_fy ? s->fye : nullptr, s->partial, &nblk, s->st));
@@ -1912,12 +1939,12 @@ tph_status tph_lithostatic_pressure(tph_solver* s, const double* rho_b, double g
     if (!rho_b || !p) { set_error("rho_b and p are required"); return TPH_ERR_INVALID; }
     if (!std::isfinite(gy)) { set_error("gravity must be finite"); return TPH_ERR_INVALID; }
     const Geom& g = s->lev[0].g;
-    TPH_TRY(copy_in(s, g, s->gtmp[2], rho_b));
+    TPH_TRY(copy_in(s, g, {{s->gtmp[2], rho_b}}));
     const Vec3 t = vec3(s, s->t3);
     TPH_HIP(hipMemsetAsync(s->t3, 0, s->n3 * sizeof(double), s->st));
     TPH_HIP(launch_lithostatic(g, s->gtmp[2], gy, t.p(), s->st));
     TPH_TRY(remove_pressure_mean(s, s->t3));
-    TPH_TRY(copy_out(s, g, p, t.p()));
+    TPH_TRY(copy_out(s, g, {{p, t.p()}}));
     TPH_HIP(hipStreamSynchronize(s->st));
     return TPH_OK;
 }
@@ -1953,7 +1980,7 @@ tph_status tph_solve_continuation(tph_solver* s, const double* eta_b, const doub
     // initial guess: the lithostatic pressure with zero velocity, or the caller's fields
     if (lithostatic) {
         TPH_HIP(hipMemsetAsync(s->x, 0, s->n3 * sizeof(double), s->st));
-        TPH_TRY(copy_in(s, g, s->gtmp[2], rho_b));
+        TPH_TRY(copy_in(s, g, {{s->gtmp[2], rho_b}}));
         TPH_HIP(launch_lithostatic(g, s->gtmp[2], gy, vec3(s, s->x).p(), s->st));
     } else {
         TPH_TRY(load_solution(s, s->x, vx, vy, p));
@@ -2048,9 +2075,7 @@ tph_status tph_precondition_apply(tph_solver* s, const double* rx, const double*
     }
     const Geom& g = s->lev[0].g;
     Vec3 r = vec3(s, s->b2);
-    TPH_TRY(copy_in(s, g, r.vx(), rx));
-    TPH_TRY(copy_in(s, g, r.vy(), ry));
-    TPH_TRY(copy_in(s, g, r.p(), rp));
+    TPH_TRY(copy_in(s, g, {{r.vx(), rx}, {r.vy(), ry}, {r.p(), rp}}));
     // z and w in the accelerator workspace, free outside a solve: z (a
     // solution-type vector, mirrored ghosts) in the first preconditioned
     // slot, w (residual-type) in the second basis slot.  Basis vectors must
@@ -2074,9 +2099,7 @@ tph_status tph_precondition(tph_solver* s, const double* rx, const double* ry, c
     if (!rx || !ry || !rp || !zx || !zy || !zp) { set_error("all six arrays are required"); return TPH_ERR_INVALID; }
     const Geom& g = s->lev[0].g;
     Vec3 r = vec3(s, s->t2);
-    TPH_TRY(copy_in(s, g, r.vx(), rx));
-    TPH_TRY(copy_in(s, g, r.vy(), ry));
-    TPH_TRY(copy_in(s, g, r.p(), rp));
+    TPH_TRY(copy_in(s, g, {{r.vx(), rx}, {r.vy(), ry}, {r.p(), rp}}));
     TPH_HIP(hipMemsetAsync(s->t1, 0, s->n3 * sizeof(double), s->st));
     TPH_TRY(precondition(s, s->t2, s->t1, false));
     TPH_TRY(store_solution(s, s->t1, zx, zy, zp));
@@ -2129,8 +2152,7 @@ tph_status tph_level_viscosity(tph_solver* s, int32_t level, double* eta_b, doub
     TPH_TRY(require_ready(s));
     if (level < 0 || level >= s->nlev) { set_error("level out of range"); return TPH_ERR_INVALID; }
     const LevelBuf& L = s->lev[level];
-    if (eta_b) TPH_TRY(copy_out(s, L.g, eta_b, L.eb64));
-    if (eta_p) TPH_TRY(copy_out(s, L.g, eta_p, L.ep64));
+    TPH_TRY(copy_out(s, L.g, {{eta_b, L.eb64}, {eta_p, L.ep64}}));
     TPH_HIP(hipStreamSynchronize(s->st));
     return TPH_OK;
 }
@@ -2144,9 +2166,7 @@ tph_status tph_solve_adjoint(tph_solver* s, const double* gvx, const double* gvy
     TPH_HIP(hipMemsetAsync(s->b2, 0, s->n3 * sizeof(double), s->st));
     const Geom& g = s->lev[0].g;
     Vec3 r = vec3(s, s->b2);
-    if (gvx) TPH_TRY(copy_in(s, g, r.vx(), gvx));
-    if (gvy) TPH_TRY(copy_in(s, g, r.vy(), gvy));
-    if (gp) TPH_TRY(copy_in(s, g, r.p(), gp));
+    TPH_TRY(copy_in(s, g, {{r.vx(), gvx}, {r.vy(), gvy}, {r.p(), gp}}));
     // the output pressure of a solve is mean-free and ghosts mirror their owners:
     // project the incoming gradient accordingly (this also makes the system consistent)
     TPH_HIP(launch_fold_ghost_grad(g, r, s->st));
@@ -2171,9 +2191,7 @@ tph_status tph_coeff_gradient(tph_solver* s, const double* vx, const double* vy,
         TPH_HIP(hipMemsetAsync(s->gtmp[k] - (kAlign - 1), 0, field_alloc(g) * sizeof(double), s->st));
     TPH_HIP(launch_coeff_gradient(g, vec3(s, s->t1), vec3(s, s->t2), s->gx, s->gy, g_eta_b ? s->gtmp[0] : nullptr,
                                   g_eta_p ? s->gtmp[1] : nullptr, g_rho_b ? s->gtmp[2] : nullptr, s->st));
-    if (g_eta_b) TPH_TRY(copy_out(s, g, g_eta_b, s->gtmp[0]));
-    if (g_eta_p) TPH_TRY(copy_out(s, g, g_eta_p, s->gtmp[1]));
-    if (g_rho_b) TPH_TRY(copy_out(s, g, g_rho_b, s->gtmp[2]));
+    TPH_TRY(copy_out(s, g, {{g_eta_b, s->gtmp[0]}, {g_eta_p, s->gtmp[1]}, {g_rho_b, s->gtmp[2]}}));
     TPH_HIP(hipStreamSynchronize(s->st));
     return TPH_OK;
 }
