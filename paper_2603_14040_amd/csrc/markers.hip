@@ -725,20 +725,43 @@ __global__ __launch_bounds__(kNodeWaves * 64) void k_nodes(NodeGrid q, int nx, i
     node(i0, top[0], top[1]);
 }
 
+// two neighbouring entries of a row, wherever the pair starts
+typedef double Pair __attribute__((ext_vector_type(2), aligned(8)));
+
+// the four nodes of the cell that a marker was last interpolated in
+struct Cell {
+    uint32_t at;                   // its first node; none: ~0
+    Pair a, b;
+};
+
 // (the cell found by a multiplication may differ from the divided one for a
-// marker on a cell edge; both cells give the same value there)
-__device__ __forceinline__ double interp(const NodeGrid& q, const double* __restrict__ grid, double x, double y) {
+// marker on a cell edge; both cells give the same value there).  Within the node
+// range the parts of the cell are in [0, 1) by themselves; only a wave with a
+// marker outside it clamps.  A row's two nodes in one load, and two
+// interpolations along x and one along y: six operations.
+__device__ __forceinline__ double interp(const NodeGrid& q, const double* __restrict__ grid, double x, double y,
+                                         Cell& c) {
     const double tx = (x - q.x0) * q.idx, ty = (y - q.y0) * q.idy;
-    int j = (int)floor(tx);
-    int i = (int)floor(ty);
-    j = j < q.jmin ? q.jmin : (j > q.jmax - 1 ? q.jmax - 1 : j);
-    i = i < q.imin ? q.imin : (i > q.imax - 1 ? q.imax - 1 : i);
-    double rx = tx - j, ry = ty - i;
-    rx = rx < 0.0 ? 0.0 : (rx > 1.0 ? 1.0 : rx);
-    ry = ry < 0.0 ? 0.0 : (ry > 1.0 ? 1.0 : ry);
-    const double* g0 = grid + (size_t)i * q.pitch + j;
-    const double* g1 = g0 + q.pitch;
-    return (1.0 - rx) * (1.0 - ry) * g0[0] + rx * (1.0 - ry) * g0[1] + (1.0 - rx) * ry * g1[0] + rx * ry * g1[1];
+    const double fx = floor(tx), fy = floor(ty);
+    int j = (int)fx, i = (int)fy;
+    double rx = tx - fx, ry = ty - fy;
+    if (j < q.jmin || j > q.jmax - 1 || i < q.imin || i > q.imax - 1) {
+        j = j < q.jmin ? q.jmin : (j > q.jmax - 1 ? q.jmax - 1 : j);
+        i = i < q.imin ? q.imin : (i > q.imax - 1 ? q.imax - 1 : i);
+        rx = tx - j;
+        ry = ty - i;
+        rx = rx < 0.0 ? 0.0 : (rx > 1.0 ? 1.0 : rx);
+        ry = ry < 0.0 ? 0.0 : (ry > 1.0 ? 1.0 : ry);
+    }
+    const uint32_t at = (uint32_t)(i * q.pitch + j);
+    if (at != c.at) {
+        const double* g0 = grid + at;
+        c.at = at;
+        c.a = *(const Pair*)g0;
+        c.b = *(const Pair*)(g0 + q.pitch);
+    }
+    const double u = __builtin_fma(rx, c.a.y - c.a.x, c.a.x), v = __builtin_fma(rx, c.b.y - c.b.x, c.b.x);
+    return __builtin_fma(ry, v - u, u);
 }
 
 __global__ __launch_bounds__(256) void k_from_grid(NodeGrid q, int n, const double* __restrict__ xm,
@@ -746,9 +769,13 @@ __global__ __launch_bounds__(256) void k_from_grid(NodeGrid q, int n, const doub
                                                    double* __restrict__ out) {
     const int m = blockIdx.x * blockDim.x + threadIdx.x;
     if (m >= n) return;
-    out[m] = interp(q, grid, xm[m], ym[m]);
+    Cell c{~0u};
+    out[m] = interp(q, grid, xm[m], ym[m], c);
 }
 
+// Bound by the gathers of the velocity (16 loads a marker) and the latency of four of them in a row.  A
+// stage moves a marker by a fraction of a cell in a usual step: most lanes are still in the cell of the
+// stage before and keep its nodes.
 __global__ __launch_bounds__(256) void k_rk4(NodeGrid qx, NodeGrid qy, double lx, double ly, int n,
                                              double* __restrict__ xm, double* __restrict__ ym,
                                              const double* __restrict__ vx, const double* __restrict__ vy, double dt) {
@@ -757,15 +784,16 @@ __global__ __launch_bounds__(256) void k_rk4(NodeGrid qx, NodeGrid qy, double lx
     auto clampx = [&](double v) { return v < 0.0 ? 0.0 : (v > lx ? lx : v); };
     auto clampy = [&](double v) { return v < 0.0 ? 0.0 : (v > ly ? ly : v); };
     const double x = xm[m], y = ym[m];
-    const double k1x = interp(qx, vx, x, y), k1y = interp(qy, vy, x, y);
+    Cell cx{~0u}, cy{~0u};
+    const double k1x = interp(qx, vx, x, y, cx), k1y = interp(qy, vy, x, y, cy);
     double sx = clampx(x + 0.5 * dt * k1x), sy = clampy(y + 0.5 * dt * k1y);
-    const double k2x = interp(qx, vx, sx, sy), k2y = interp(qy, vy, sx, sy);
+    const double k2x = interp(qx, vx, sx, sy, cx), k2y = interp(qy, vy, sx, sy, cy);
     sx = clampx(x + 0.5 * dt * k2x);
     sy = clampy(y + 0.5 * dt * k2y);
-    const double k3x = interp(qx, vx, sx, sy), k3y = interp(qy, vy, sx, sy);
+    const double k3x = interp(qx, vx, sx, sy, cx), k3y = interp(qy, vy, sx, sy, cy);
     sx = clampx(x + dt * k3x);
     sy = clampy(y + dt * k3y);
-    const double k4x = interp(qx, vx, sx, sy), k4y = interp(qy, vy, sx, sy);
+    const double k4x = interp(qx, vx, sx, sy, cx), k4y = interp(qy, vy, sx, sy, cy);
     xm[m] = clampx(x + dt / 6.0 * (k1x + 2.0 * k2x + 2.0 * k3x + k4x));
     ym[m] = clampy(y + dt / 6.0 * (k1y + 2.0 * k2y + 2.0 * k3y + k4y));
 }
