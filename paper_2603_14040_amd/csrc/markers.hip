@@ -367,9 +367,10 @@ __device__ __forceinline__ int lower_bound(const uint32_t* __restrict__ keys, in
 // Markers of one bucket (2^shift cells) to the order of the cells, and cstart of its cells.  A bucket of
 // up to 10240 markers is ranked once, in registers; a longer one is counted first and goes in pieces.
 // K as in k_digit_scatter: the bucket's run comes from the digit totals (uint16_t), or from a search in
-// the sorted keys (uint32_t).
+// the sorted keys (uint32_t).  1024^2 cells, 16 markers each: 80 us with six waves a SIMD (eight: 91 us,
+// with 20 registers spilled; five: 101 us).
 template <int NW, typename K>
-__global__ __launch_bounds__(NW * 64, 8) void k_cell_sort(const K* __restrict__ kin, const int32_t* __restrict__ vin, int n,
+__global__ __launch_bounds__(NW * 64, 6) void k_cell_sort(const K* __restrict__ kin, const int32_t* __restrict__ vin, int n,
                                                     int shift, int ncell, const int32_t* __restrict__ total,
                                                     int32_t* __restrict__ cstart, int32_t* __restrict__ order) {
     constexpr int R = kSortRounds;
@@ -531,8 +532,8 @@ __device__ __forceinline__ void divided_factors(const NodeGrid& q, int nx, doubl
 // above's are kept in registers, those of the wave before come through
 // LDS.  Lane 0 of a wave is a cell for the node of lane 1 only, and a
 // workgroup's first cell row is the last one of the workgroup above.
-// Bound by the gathers (28 B a marker) and, nearly as much, by the vector
-// operations.
+// Bound by the gathers (28 B a marker: 95 us at the rate of a copy at 1024^2 cells of 16 markers; 146 us,
+// from 173 with a pass over partial sums in memory) and by the walk's operations.
 // ---------------------------------------------------------------------------
 constexpr int kNodeWaves = 4;
 __device__ __forceinline__ int stage_slot(int t) { return t + (t >> 4); }
@@ -829,8 +830,8 @@ struct BinPlan {
 BinPlan bin_plan(const tph_markers* h) {
     const int ncell = (h->nx + 1) * (h->ny + 1);
     BinPlan p;
-    // as many buckets as one pass can tell apart: with 512 cells each at 1024^2 x 16 markers k_cell_sort takes 92 us, with
-    // 1024 cells 131 us, and the other kernels 8 us less
+    // as many buckets as one pass can tell apart: with 512 cells each at 1024^2 x 16 markers k_cell_sort takes 80 us, with
+    // 1024 cells some 40 us more, and the other kernels 8 us less
     p.shift = kMinShift;
     auto count = [&] { return (int)(((long long)ncell + (1ll << p.shift) - 1) >> p.shift); };
     while (p.shift < kMaxShift && count() > kMaxBuckets) ++p.shift;
