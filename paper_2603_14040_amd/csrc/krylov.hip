@@ -79,46 +79,38 @@ __global__ __launch_bounds__(256) void k_multidot(const double* __restrict__ V0,
         partial[(size_t)(v < nv ? v : norm_slot) * nblk + blockIdx.x] = s;
 }
 
+// Sums of U rows of at most kSumBlocks block sums (r, r + step, .. below k; valid in lane 0): a wave a row, the
+// entries summed as by a workgroup with a thread for each.
+constexpr int kSumBlocks = 128;
+template <int U>
+__device__ __forceinline__ void wave_row_sums(const double* __restrict__ partial, int nblk, int k, int r, int step,
+                                              double (&t)[U]) {
+    const int lane = threadIdx.x & 63;
+    constexpr int Q = kSumBlocks / 64;
+    double v[U][Q];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int b = q * 64 + lane;
+            v[u][q] = b < nblk ? partial[(size_t)min(r + u * step, k - 1) * nblk + b] : 0.0;
+        }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        t[u] = 0.0;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) t[u] += wave_sum(0.0 + v[u][q]);
+    }
+}
+
 // w -= sum_i h[i] V_i for any number of vectors, with the block sums of the new
 // w . w, in one pass over w (8 vectors' loads in flight at a time; a launch per 8
-// vectors re-read w and paid 5 us each on short vectors).
-// SUMS: h is not there yet.  Every workgroup adds up the rows of block sums that it comes from by
-// itself, a row per wave and in k_reduce_rows' order, and the first one writes them out: for the few blocks
-// of a small grid (at most kSumBlocks) that takes 1 us where a launch for it took 4.
-constexpr int kSumBlocks = 128;
-template <bool SUMS>
+// vectors re-read w and paid 5 us each on short vectors)
 __global__ __launch_bounds__(256) void k_axpy_norm(double* __restrict__ w, const double* __restrict__ V0,
                                                   size_t vstride, int nv, const double* __restrict__ h, size_t n,
-                                                  double* __restrict__ partial, RowSums rows, Again again) {
+                                                  double* __restrict__ partial, Again again) {
     __shared__ double part[4];
-    __shared__ double hs[kMaxRestart + 2];
     if (again.asked() && !again.needed()) return;
-    if (SUMS) {
-        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-        constexpr int U = 4, Q = kSumBlocks / 64;        // rows in flight per wave, entries of a lane
-        for (int r0 = wave; r0 < rows.k; r0 += 4 * U) {
-            double v[U][Q];
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-#pragma unroll
-                for (int q = 0; q < Q; ++q) {
-                    const int r = min(r0 + 4 * u, rows.k - 1), b = q * 64 + lane;
-                    v[u][q] = b < rows.nblk ? rows.partial[(size_t)r * rows.nblk + b] : 0.0;
-                }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                double t = 0.0;
-#pragma unroll
-                for (int q = 0; q < Q; ++q) t += wave_sum(0.0 + v[u][q]);
-                if (lane == 0 && r0 + 4 * u < rows.k) hs[r0 + 4 * u] = t;
-            }
-        }
-        __syncthreads();
-        if (blockIdx.x == 0 && (int)threadIdx.x < rows.k) {
-            rows.out[threadIdx.x] = hs[threadIdx.x];
-            rows.host[threadIdx.x] = hs[threadIdx.x];
-        }
-    }
     double acc[1] = {0.0};
     const size_t step = (size_t)gridDim.x * 256;
     constexpr int U = 4;
@@ -139,7 +131,7 @@ __global__ __launch_bounds__(256) void k_axpy_norm(double* __restrict__ w, const
                     y[u][v] = in[u] && v0 + v < nv ? V0[(v0 + v) * vstride + t0 + u * step] : 0.0;
 #pragma unroll
             for (int v = 0; v < kNV; ++v) {
-                const double hv = v0 + v < nv ? (SUMS ? hs[v0 + v] : h[v0 + v]) : 0.0;
+                const double hv = v0 + v < nv ? h[v0 + v] : 0.0;
 #pragma unroll
                 for (int u = 0; u < U; ++u) x[u] -= hv * y[u][v];
             }
@@ -155,8 +147,88 @@ __global__ __launch_bounds__(256) void k_axpy_norm(double* __restrict__ w, const
     if (threadIdx.x == 0) partial[blockIdx.x] = s;
 }
 
+// The same where h is not there yet, for vectors of at most kSumBlocks blocks (short ones: at most 8 entries a
+// thread, byte offsets of 32 bits).  Every workgroup adds up the rows of block sums that h comes from by
+// itself and the first one writes them out: that takes 1 us where a launch for it took 4.
+// Bound by latency and by what a load costs to issue: vectors in uniform bases, a thread past the end
+// reading the last entry (64-bit addresses and a mask per load took 8.8 us at 13 blocks and some 17 vectors, now 7.6).
+__global__ __launch_bounds__(256) void k_axpy_norm_sums(double* __restrict__ w, const double* __restrict__ V0,
+                                                       size_t vstride, int nv, unsigned n,
+                                                       double* __restrict__ partial, RowSums rows, Again again) {
+    __shared__ double part[4];
+    __shared__ double hs[kMaxRestart + 2];
+    if (again.asked() && !again.needed()) return;
+    constexpr int RU = 4;                                // rows in flight per wave
+    for (int r = threadIdx.x >> 6; r < rows.k; r += 4 * RU) {
+        double t[RU];
+        wave_row_sums<RU>(rows.partial, rows.nblk, rows.k, r, 4, t);
+#pragma unroll
+        for (int u = 0; u < RU; ++u)
+            if ((threadIdx.x & 63) == 0 && r + 4 * u < rows.k) hs[r + 4 * u] = t[u];
+    }
+    __syncthreads();
+    if (blockIdx.x == 0 && (int)threadIdx.x < rows.k) {
+        rows.out[threadIdx.x] = hs[threadIdx.x];
+        rows.host[threadIdx.x] = hs[threadIdx.x];
+    }
+    double acc[1] = {0.0};
+    const unsigned step = gridDim.x * 256;
+    constexpr int U = 4;
+    auto entry = [](const double* base, unsigned byte) -> const double& { return *(const double*)((const char*)base + byte); };
+    for (unsigned t0 = blockIdx.x * 256 + threadIdx.x; t0 < n; t0 += U * step) {
+        double x[U];
+        unsigned at[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            at[u] = min(t0 + u * step, n - 1) * 8u;
+            x[u] = entry(w, at[u]);
+        }
+        int v0 = 0;
+        for (; v0 + kNV <= nv; v0 += kNV) {
+            double y[U][kNV];
+#pragma unroll
+            for (int v = 0; v < kNV; ++v)
+#pragma unroll
+                for (int u = 0; u < U; ++u) y[u][v] = entry(V0 + (v0 + v) * vstride, at[u]);
+#pragma unroll
+            for (int v = 0; v < kNV; ++v) {
+                const double hv = hs[v0 + v];
+#pragma unroll
+                for (int u = 0; u < U; ++u) x[u] -= hv * y[u][v];
+            }
+        }
+        for (; v0 + 2 <= nv; v0 += 2) {
+            double y[U][2];
+#pragma unroll
+            for (int v = 0; v < 2; ++v)
+#pragma unroll
+                for (int u = 0; u < U; ++u) y[u][v] = entry(V0 + (v0 + v) * vstride, at[u]);
+#pragma unroll
+            for (int v = 0; v < 2; ++v) {
+                const double hv = hs[v0 + v];
+#pragma unroll
+                for (int u = 0; u < U; ++u) x[u] -= hv * y[u][v];
+            }
+        }
+        if (v0 < nv) {
+            const double hv = hs[v0];
+#pragma unroll
+            for (int u = 0; u < U; ++u) x[u] -= hv * entry(V0 + v0 * vstride, at[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (t0 + u * step >= n) continue;
+            w[t0 + u * step] = x[u];
+            acc[0] += x[u] * x[u];
+        }
+    }
+    const double s = block_sums(acc, part);
+    if (threadIdx.x == 0) partial[blockIdx.x] = s;
+}
+
 // Row sums of partial (k rows of nblk) in one workgroup: 256 threads per row,
-// four rows at a time, each in the same fixed order.  The results go to out and,
+// four rows at a time, each in the same fixed order; rows of up to 128 entries by a
+// wave each, which sums in that order too (20 rows of 44: 6.3 -> 5.3 us).  The results go to out and,
 // where given, to mapped host memory, followed by the sequence number the host
 // polls (one launch where a workgroup per row needed a second one to post it).
 constexpr int kRowThreads = 256;
@@ -167,6 +239,22 @@ __global__ __launch_bounds__(kRowThreads * kRowGroups) void k_reduce_rows(
     __shared__ double part[kRowGroups][kRowThreads / 64];
     const int grp = threadIdx.x / kRowThreads, tid = threadIdx.x % kRowThreads;
     const bool left_out = again.asked() && !again.needed();
+    if (nblk <= kSumBlocks) {                     // short rows: sixteen at a time, a wave each
+        constexpr int U = 2, W = kRowThreads * kRowGroups / 64;
+        for (int r = threadIdx.x >> 6; r < k; r += W * U) {
+            double t[U];
+            wave_row_sums<U>(partial, nblk, k, r, W, t);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (left_out) t[u] = *again.norm2;       // the norm that stays
+                if ((threadIdx.x & 63) == 0 && r + u * W < k) {
+                    out[r + u * W] = t[u];
+                    if (host_out) host_out[r + u * W] = t[u];
+                }
+            }
+        }
+        k = 0;
+    }
     for (int r0 = 0; r0 < k; r0 += kRowGroups) {
         const int r = r0 + grp;
         double s = 0.0;
@@ -357,8 +445,7 @@ hipError_t launch_multidot(const double* V0, size_t vstride, int nv, const doubl
 
 hipError_t launch_axpy_norm(double* w, const double* V0, size_t vstride, int nv, const double* h, size_t n,
                             double* partial, int nblk, hipStream_t st, Again again) {
-    hipLaunchKernelGGL((k_axpy_norm<false>), dim3(nblk), dim3(256), 0, st, w, V0, vstride, nv, h, n, partial, RowSums{},
-                       again);
+    hipLaunchKernelGGL(k_axpy_norm, dim3(nblk), dim3(256), 0, st, w, V0, vstride, nv, h, n, partial, again);
     return hipGetLastError();
 }
 
@@ -366,10 +453,10 @@ int sum_blocks_max() { return kSumBlocks; }
 
 hipError_t launch_axpy_norm_sums(double* w, const double* V0, size_t vstride, int nv, const RowSums& rows, size_t n,
                                  double* partial, hipStream_t st, Again again) {
-    if (rows.nblk < 1 || rows.nblk > kSumBlocks || rows.k < nv || rows.k < 1 || rows.k > kMaxRestart + 2)
+    if (rows.nblk < 1 || rows.nblk > kSumBlocks || n < 1 || n > (size_t)kSumBlocks * 2048 || rows.k < nv || rows.k < 1 || rows.k > kMaxRestart + 2)
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_axpy_norm<true>), dim3(rows.nblk), dim3(256), 0, st, w, V0, vstride, nv, nullptr, n, partial,
-                       rows, again);
+    hipLaunchKernelGGL(k_axpy_norm_sums, dim3(rows.nblk), dim3(256), 0, st, w, V0, vstride, nv, (unsigned)n, partial, rows,
+                       again);
     return hipGetLastError();
 }
 
