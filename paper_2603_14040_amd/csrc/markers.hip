@@ -729,19 +729,17 @@ __global__ __launch_bounds__(kNodeWaves * 64) void k_nodes(NodeGrid q, int nx, i
 // two neighbouring entries of a row, wherever the pair starts
 typedef double Pair __attribute__((ext_vector_type(2), aligned(8)));
 
-// the four nodes of the cell that a marker was last interpolated in
-struct Cell {
-    uint32_t at;                   // its first node; none: ~0
-    Pair a, b;
+// where a marker is in a node grid: the first node of its cell, and its parts of the cell
+struct Place {
+    uint32_t at;
+    double rx, ry;
 };
 
 // (the cell found by a multiplication may differ from the divided one for a
 // marker on a cell edge; both cells give the same value there).  Within the node
 // range the parts of the cell are in [0, 1) by themselves; only a wave with a
-// marker outside it clamps.  A row's two nodes in one load, and two
-// interpolations along x and one along y: six operations.
-__device__ __forceinline__ double interp(const NodeGrid& q, const double* __restrict__ grid, double x, double y,
-                                         Cell& c) {
+// marker outside it clamps.
+__device__ __forceinline__ Place place(const NodeGrid& q, double x, double y) {
     const double tx = (x - q.x0) * q.idx, ty = (y - q.y0) * q.idy;
     const double fx = floor(tx), fy = floor(ty);
     int j = (int)fx, i = (int)fy;
@@ -754,15 +752,22 @@ __device__ __forceinline__ double interp(const NodeGrid& q, const double* __rest
         rx = rx < 0.0 ? 0.0 : (rx > 1.0 ? 1.0 : rx);
         ry = ry < 0.0 ? 0.0 : (ry > 1.0 ? 1.0 : ry);
     }
-    const uint32_t at = (uint32_t)(i * q.pitch + j);
-    if (at != c.at) {
-        const double* g0 = grid + at;
-        c.at = at;
-        c.a = *(const Pair*)g0;
-        c.b = *(const Pair*)(g0 + q.pitch);
-    }
-    const double u = __builtin_fma(rx, c.a.y - c.a.x, c.a.x), v = __builtin_fma(rx, c.b.y - c.b.x, c.b.x);
-    return __builtin_fma(ry, v - u, u);
+    return {(uint32_t)(i * q.pitch + j), rx, ry};
+}
+
+// the four nodes of a cell: a row's two in one load
+struct Cell {
+    Pair a, b;
+};
+__device__ __forceinline__ Cell cell_of(const NodeGrid& q, const double* __restrict__ grid, uint32_t at) {
+    const double* g0 = grid + at;
+    return {*(const Pair*)g0, *(const Pair*)(g0 + q.pitch)};
+}
+
+// two interpolations along x and one along y: six operations
+__device__ __forceinline__ double interp(const Cell& c, const Place& m) {
+    const double u = __builtin_fma(m.rx, c.a.y - c.a.x, c.a.x), v = __builtin_fma(m.rx, c.b.y - c.b.x, c.b.x);
+    return __builtin_fma(m.ry, v - u, u);
 }
 
 __global__ __launch_bounds__(256) void k_from_grid(NodeGrid q, int n, const double* __restrict__ xm,
@@ -770,8 +775,8 @@ __global__ __launch_bounds__(256) void k_from_grid(NodeGrid q, int n, const doub
                                                    double* __restrict__ out) {
     const int m = blockIdx.x * blockDim.x + threadIdx.x;
     if (m >= n) return;
-    Cell c{~0u};
-    out[m] = interp(q, grid, xm[m], ym[m], c);
+    const Place at = place(q, xm[m], ym[m]);
+    out[m] = interp(cell_of(q, grid, at.at), at);
 }
 
 // Bound by the gathers of the velocity (16 loads a marker) and the latency of four of them in a row.  A
@@ -785,16 +790,30 @@ __global__ __launch_bounds__(256) void k_rk4(NodeGrid qx, NodeGrid qy, double lx
     auto clampx = [&](double v) { return v < 0.0 ? 0.0 : (v > lx ? lx : v); };
     auto clampy = [&](double v) { return v < 0.0 ? 0.0 : (v > ly ? ly : v); };
     const double x = xm[m], y = ym[m];
-    Cell cx{~0u}, cy{~0u};
-    const double k1x = interp(qx, vx, x, y, cx), k1y = interp(qy, vy, x, y, cy);
+    Place px = place(qx, x, y), py = place(qy, x, y);
+    Cell cx = cell_of(qx, vx, px.at), cy = cell_of(qy, vy, py.at);
+    // velocity at (u, v); both components' nodes together, so that their latencies overlap
+    auto velocity = [&](double u, double v, double& kx, double& ky) {
+        const Place nx = place(qx, u, v), ny = place(qy, u, v);
+        if (nx.at != px.at || ny.at != py.at) {
+            cx = cell_of(qx, vx, nx.at);
+            cy = cell_of(qy, vy, ny.at);
+        }
+        px = nx;
+        py = ny;
+        kx = interp(cx, nx);
+        ky = interp(cy, ny);
+    };
+    const double k1x = interp(cx, px), k1y = interp(cy, py);
+    double k2x, k2y, k3x, k3y, k4x, k4y;
     double sx = clampx(x + 0.5 * dt * k1x), sy = clampy(y + 0.5 * dt * k1y);
-    const double k2x = interp(qx, vx, sx, sy, cx), k2y = interp(qy, vy, sx, sy, cy);
+    velocity(sx, sy, k2x, k2y);
     sx = clampx(x + 0.5 * dt * k2x);
     sy = clampy(y + 0.5 * dt * k2y);
-    const double k3x = interp(qx, vx, sx, sy, cx), k3y = interp(qy, vy, sx, sy, cy);
+    velocity(sx, sy, k3x, k3y);
     sx = clampx(x + dt * k3x);
     sy = clampy(y + dt * k3y);
-    const double k4x = interp(qx, vx, sx, sy, cx), k4y = interp(qy, vy, sx, sy, cy);
+    velocity(sx, sy, k4x, k4y);
     xm[m] = clampx(x + dt / 6.0 * (k1x + 2.0 * k2x + 2.0 * k3x + k4x));
     ym[m] = clampy(y + dt / 6.0 * (k1y + 2.0 * k2y + 2.0 * k3y + k4y));
 }
@@ -882,14 +901,14 @@ hipError_t launch_pass(tph_markers* h, const BinPlan& p, const NodeGrid& q, int 
     return hipGetLastError();
 }
 
-// kernels whose LDS can exceed 64 KB: granted once per handle, on its device
-hipError_t grant_lds() {
-    const void* f[] = {(const void*)&k_digit_scatter<1, uint16_t>,  (const void*)&k_digit_scatter<4, uint16_t>,
-                       (const void*)&k_digit_scatter<16, uint16_t>, (const void*)&k_cell_sort<8, uint16_t>,
-                       (const void*)&k_cell_sort<8, uint32_t>};
+// the scatter's LDS exceeds 64 KB with more than 1820 digits: granted once per handle, on its device
+hipError_t grant_lds(const BinPlan& p) {
+    const size_t lds = (size_t)p.most() * (sizeof(int) + kWaves * sizeof(uint16_t));
+    const void* f[] = {(const void*)&k_digit_scatter<1, uint16_t>, (const void*)&k_digit_scatter<4, uint16_t>,
+                       (const void*)&k_digit_scatter<16, uint16_t>};
     hipError_t e = hipSuccess;
     for (const void* k : f)
-        if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
+        if (lds > 64 * 1024 && e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     return e;
 }
 
@@ -939,7 +958,7 @@ tph_status tph_markers_create(int32_t nx, int32_t ny, double lx, double ly, int3
     get((void**)&h->hist, (size_t)ntiles * p.most() * sizeof(int32_t));
     get((void**)&h->total, (size_t)p.most() * sizeof(int32_t));
     if (e == hipSuccess) {
-        e = grant_lds();
+        e = grant_lds(p);
         what = "LDS for the binning kernels";
     }
     if (e != hipSuccess) {
