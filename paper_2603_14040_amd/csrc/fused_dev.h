@@ -348,7 +348,11 @@ __device__ __forceinline__ void gs_stages(const Geom& g, int gi0, int gj0, T* sx
                                           const T* rr, T omega, const LevelC<T>& k) {
     using S = Stages<TW, TH, H, NSTAGE>;
     constexpr int RW = TW + 2 * H, RH = TH + 2 * H;
-    const int tid = threadIdx.x;
+    int tid = threadIdx.x;
+    // Two sweeps: the indices anew, instead of those of all eight stages kept since the loads (129 registers with 64 x 16
+    // FP32 nodes from zero, one workgroup a CU; 88 without, and 32 instead of 66 with 32 x 8: 2 + 2 sweeps at
+    // 1024^2 10.9 -> 8.7 ms for 48 V-cycles).
+    if (NSTAGE > 4) asm("" : "+v"(tid));
 #pragma unroll
     for (int s = 0; s < NSTAGE; ++s) {
         const int comp = (s >> 1) & 1;
