@@ -764,10 +764,13 @@ __device__ __forceinline__ Cell cell_of(const NodeGrid& q, const double* __restr
     return {*(const Pair*)g0, *(const Pair*)(g0 + q.pitch)};
 }
 
-// two interpolations along x and one along y: six operations
+// The sum of four weighted nodes.  The weights add up to one and each product rounds by itself, so the error is
+// relative to the result whatever the ratio of the nodes, and a marker on a node gets its value.  Three
+// differences, a.x + r (a.y - a.x), are four operations fewer and round at the largest node: 2e-10 of the result
+// at a ratio of 1e6, where this gives 4e-16.
 __device__ __forceinline__ double interp(const Cell& c, const Place& m) {
-    const double u = __builtin_fma(m.rx, c.a.y - c.a.x, c.a.x), v = __builtin_fma(m.rx, c.b.y - c.b.x, c.b.x);
-    return __builtin_fma(m.ry, v - u, u);
+    const double rx = m.rx, ry = m.ry;
+    return (1.0 - rx) * (1.0 - ry) * c.a.x + rx * (1.0 - ry) * c.a.y + (1.0 - rx) * ry * c.b.x + rx * ry * c.b.y;
 }
 
 __global__ __launch_bounds__(256) void k_from_grid(NodeGrid q, int n, const double* __restrict__ xm,
