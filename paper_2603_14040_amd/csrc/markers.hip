@@ -736,21 +736,29 @@ struct Place {
 };
 
 // (the cell found by a multiplication may differ from the divided one for a
-// marker on a cell edge; both cells give the same value there).  Within the node
-// range the parts of the cell are in [0, 1) by themselves; only a wave with a
-// marker outside it clamps.
+// marker on a cell edge; both cells give the same value there).  The parts of the
+// cell come from the unrounded product, which can lie below the node line that
+// the rounded one was taken to: inside the node range they are kept from being
+// negative, and only a wave with a marker outside it, or at no position, clamps
+// both ways.
 __device__ __forceinline__ Place place(const NodeGrid& q, double x, double y) {
-    const double tx = (x - q.x0) * q.idx, ty = (y - q.y0) * q.idy;
-    const double fx = floor(tx), fy = floor(ty);
+    const double ax = x - q.x0, ay = y - q.y0;
+    double fx = floor(ax * q.idx), fy = floor(ay * q.idy);
     int j = (int)fx, i = (int)fy;
-    double rx = tx - fx, ry = ty - fy;
-    if (j < q.jmin || j > q.jmax - 1 || i < q.imin || i > q.imax - 1) {
+    double rx, ry;
+    const double any = fx + fy;                  // NaN if one is
+    // one condition, not a chain of branches
+    if (((unsigned)(j - q.jmin) >= (unsigned)(q.jmax - q.jmin)) | ((unsigned)(i - q.imin) >= (unsigned)(q.imax - q.imin)) |
+        (any != any)) {
         j = j < q.jmin ? q.jmin : (j > q.jmax - 1 ? q.jmax - 1 : j);
         i = i < q.imin ? q.imin : (i > q.imax - 1 ? q.imax - 1 : i);
-        rx = tx - j;
-        ry = ty - i;
+        rx = __builtin_fma(ax, q.idx, -(double)j);
+        ry = __builtin_fma(ay, q.idy, -(double)i);
         rx = rx < 0.0 ? 0.0 : (rx > 1.0 ? 1.0 : rx);
         ry = ry < 0.0 ? 0.0 : (ry > 1.0 ? 1.0 : ry);
+    } else {
+        rx = __builtin_fmax(__builtin_fma(ax, q.idx, -fx), 0.0);
+        ry = __builtin_fmax(__builtin_fma(ay, q.idy, -fy), 0.0);
     }
     return {(uint32_t)(i * q.pitch + j), rx, ry};
 }
@@ -767,10 +775,11 @@ __device__ __forceinline__ Cell cell_of(const NodeGrid& q, const double* __restr
 // The sum of four weighted nodes.  The weights add up to one and each product rounds by itself, so the error is
 // relative to the result whatever the ratio of the nodes, and a marker on a node gets its value.  Three
 // differences, a.x + r (a.y - a.x), are four operations fewer and round at the largest node: 2e-10 of the result
-// at a ratio of 1e6, where this gives 4e-16.
+// at a ratio of 1e6, where this gives 4e-16.  The fused operations are spelled out: their order decides the bits.
 __device__ __forceinline__ double interp(const Cell& c, const Place& m) {
     const double rx = m.rx, ry = m.ry;
-    return (1.0 - rx) * (1.0 - ry) * c.a.x + rx * (1.0 - ry) * c.a.y + (1.0 - rx) * ry * c.b.x + rx * ry * c.b.y;
+    const double sx = 1.0 - rx, sy = 1.0 - ry;
+    return __builtin_fma(rx * ry, c.b.y, __builtin_fma(sx * ry, c.b.x, __builtin_fma(sx * sy, c.a.x, rx * sy * c.a.y)));
 }
 
 __global__ __launch_bounds__(256) void k_from_grid(NodeGrid q, int n, const double* __restrict__ xm,

@@ -75,3 +75,23 @@ def test_infinite_and_huge_nodes():
     assert np.isposinf(m.from_grid("basic", T(x), T(y), T(grid)).cpu().numpy()).all()
     assert np.array_equal(m.from_grid("basic", T(x), T(y), T(big)).cpu().numpy(), [0.0, -2.0 ** 1022])
     m.close()
+
+
+@pytest.mark.parametrize("kind", ["basic", "cell", "vx", "vy"])
+@pytest.mark.parametrize("nx,ny", [(10, 7), (30, 49)])
+def test_no_weight_is_negative(kind, nx, ny):
+    """Markers on node lines of a spacing that is no power of two: the scaled position rounds to either side of
+    the line.  Node values are not left behind, whatever the neighbours (1 and 1e20 in turn)."""
+    g = st.Grid(nx, ny)
+    xs = np.arange(2 * nx + 1) * (0.5 * g.dx)
+    ys = np.arange(2 * ny + 1) * (0.5 * g.dy)
+    xm, ym = (a.ravel() for a in np.meshgrid(np.concatenate([xs, np.nextafter(xs, 0)]),
+                                             np.concatenate([ys, np.nextafter(ys, 0)])))
+    xm, ym = xm.clip(0, 1), ym.clip(0, 1)
+    m = tph.Markers(nx, ny, capacity=xm.size)
+    for flip in (0, 1):
+        grid = np.where((np.add.outer(np.arange(ny + 2), np.arange(nx + 2)) + flip) % 2, 1e20, 1.0)
+        got = m.from_grid(kind, T(xm), T(ym), T(grid)).cpu().numpy()
+        # the weights add up to one but for the rounding of the two products and three sums
+        assert got.min() > 1 - 1e-15 and got.max() < 1e20 * (1 + 1e-15)
+    m.close()
