@@ -551,8 +551,6 @@ tph_status build_tables_t(tph_batch* b) {
     B_TRY(b_alloc(b, &b->d_cargs, ca.size() * sizeof(CoarseArgs<T>)));
     B_HIP(hipMemcpy(b->d_cargs, ca.data(), ca.size() * sizeof(CoarseArgs<T>), hipMemcpyHostToDevice));
     b->coarse_lds = lds;
-    if (lds > 64 * 1024) B_HIP(hipFuncSetAttribute(tail_kernel<T>(b->tail), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                   (int)lds));
     return TPH_OK;
 }
 

@@ -39,28 +39,8 @@ __global__ __launch_bounds__(NT) void k_coarse_cycle(CoarseArgs<T> A) {
     coarse_cycle_body<T, NT, KP>(A);
 }
 
-// One launch; the kernel's dynamic LDS limit is raised when a launch needs
-// more than 64 KB.  The attribute is per function (and device), so it is set
-// only when a launch needs more than any earlier one on this device.
 template <typename T, int NT, int KP>
 hipError_t launch_tail(const CoarseArgs<T>& a, size_t lds_bytes, hipStream_t st) {
-    static thread_local int dev_cached = -1;
-    static thread_local size_t granted = 64 * 1024;
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return hipGetLastError();
-    if (dev != dev_cached) {
-        dev_cached = dev;
-        granted = 64 * 1024;
-    }
-    if (lds_bytes > granted) {
-        const hipError_t e = hipFuncSetAttribute((const void*)k_coarse_cycle<T, NT, KP>,
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
-        if (e != hipSuccess) {
-            (void)hipGetLastError();   // do not leave the error pending for unrelated later launches
-            return e;
-        }
-        granted = lds_bytes;
-    }
     hipLaunchKernelGGL((k_coarse_cycle<T, NT, KP>), dim3(1), dim3(NT), lds_bytes, st, a);
     return hipGetLastError();
 }
@@ -125,7 +105,7 @@ hipError_t launch_res_restrict(const Geom& gf, const Geom& gc, const T* ex, cons
 template <typename T>
 hipError_t launch_coarse_cycle(const CoarseArgs<T>& a, size_t lds_bytes, hipStream_t st) {
     const TailShape sh = coarse_cycle_shape(a.lv[0].nx, a.lv[0].ny);
-    if ((a.lv[0].nx / 2) * a.lv[0].ny > sh.threads * sh.pairs) return hipErrorInvalidValue;
+    if ((a.lv[0].nx / 2) * a.lv[0].ny > sh.threads * sh.pairs || lds_bytes > kTailLdsMax) return hipErrorInvalidValue;
     if (sh.threads == 256) return launch_tail<T, 256, 1>(a, lds_bytes, st);
     if (sh.pairs == 1) return launch_tail<T, 512, 1>(a, lds_bytes, st);
     if (sh.pairs == 2) return launch_tail<T, 512, 2>(a, lds_bytes, st);

@@ -284,7 +284,9 @@ struct CoarseArgs {
     T* ey;
     const double* Minv;
 };
-// LDS of the tail over levels g[0 .. nl-1] with nc coarsest unknowns
+// LDS of the tail over levels g[0 .. nl-1] with nc coarsest unknowns.  The levels that qualify for the tail need
+// 64232 bytes at most (88 x 40 cells in FP32): a launch asks for no more than every kernel may have.
+constexpr size_t kTailLdsMax = 64 * 1024;
 template <typename T>
 size_t coarse_cycle_lds_bytes(const Geom* g, int nl, int nc);
 // threads per workgroup and cell pairs per thread of the tail with top level g

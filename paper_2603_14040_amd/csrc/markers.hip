@@ -889,12 +889,15 @@ long long tiles_of(long long n) {
     return (n + t - 1) / t;
 }
 
+// LDS of a scatter pass with that many digits
+constexpr size_t scatter_lds(int ndig) { return (size_t)ndig * (sizeof(int) + kWaves * sizeof(uint16_t)); }
+
 template <int R>
 hipError_t launch_pass(tph_markers* h, const BinPlan& p, const NodeGrid& q, int pass) {
     const int ntiles = (int)tiles_of(h->n), n = h->n;
     const int shift = p.shift + (pass ? p.bits[0] : 0), bits = p.bits[pass], ndig = p.ndig[pass];
     const uint32_t mask = (1u << bits) - 1u;
-    const size_t lds = (size_t)ndig * (sizeof(int) + kWaves * sizeof(uint16_t));
+    const size_t lds = scatter_lds(ndig);
     if (pass == 0)
         hipLaunchKernelGGL((k_keys<R>), dim3(ntiles), dim3(1024), 0, h->st, q, h->nx, h->ny, n, h->xm, h->ym, shift, mask,
                            ndig, h->keys[0], h->hist);
@@ -913,14 +916,14 @@ hipError_t launch_pass(tph_markers* h, const BinPlan& p, const NodeGrid& q, int 
     return hipGetLastError();
 }
 
-// the scatter's LDS exceeds 64 KB with more than 1820 digits: granted once per handle, on its device
-hipError_t grant_lds(const BinPlan& p) {
-    const size_t lds = (size_t)p.most() * (sizeof(int) + kWaves * sizeof(uint16_t));
+// The scatter's LDS exceeds 64 KB with more than 1820 digits.  The limit belongs to the function, not to a handle:
+// every handle asks for the most that any of them can need, so that none lowers it under another.
+hipError_t grant_lds() {
     const void* f[] = {(const void*)&k_digit_scatter<1, uint16_t>, (const void*)&k_digit_scatter<4, uint16_t>,
                        (const void*)&k_digit_scatter<16, uint16_t>};
     hipError_t e = hipSuccess;
     for (const void* k : f)
-        if (lds > 64 * 1024 && e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)scatter_lds(kMaxBuckets));
     return e;
 }
 
@@ -970,7 +973,7 @@ tph_status tph_markers_create(int32_t nx, int32_t ny, double lx, double ly, int3
     get((void**)&h->hist, (size_t)ntiles * p.most() * sizeof(int32_t));
     get((void**)&h->total, (size_t)p.most() * sizeof(int32_t));
     if (e == hipSuccess) {
-        e = grant_lds(p);
+        e = grant_lds();
         what = "LDS for the binning kernels";
     }
     if (e != hipSuccess) {

@@ -1564,6 +1564,7 @@ tph_status create_impl(const tph_desc* desc, void* stream, tph_solver* s) {
                 if (eligible(l)) s->lc = l;
         }
         if (s->lc >= 0) s->lc_lds = need(s->lc);
+        if (s->lc_lds > kTailLdsMax) { set_error("the coarse tail exceeds its LDS"); return TPH_ERR_UNSUPPORTED; }
     }
     s->msw_mask = 0;
     s->shape_mask = 0;
