@@ -512,9 +512,9 @@ tph_status tph_markers_bin(tph_markers* h, int32_t kind, int32_t n, const double
  * node (i, j) of the binned kind (normalised bilinear average), `fill` where
  * none does; entries outside the kind's node range are not written.
  * Weights that fall on nodes outside the range are dropped (the
- * normalisation absorbs them).  No floating-point atomics: per-cell sums in
- * sorted order, then per-node sums of its four cells in a fixed order, so the
- * result is bitwise reproducible. */
+ * normalisation absorbs them).  No floating-point atomics: per-cell sums, then
+ * per-node sums of its four cells, each in a fixed order, so the result is
+ * bitwise reproducible. */
 tph_status tph_markers_to_grid(tph_markers* h, const double* phi_m, double fill, double* grid);
 
 /* Grid -> marker: phi_m = the bilinear interpolation of the `kind` node

@@ -5,7 +5,7 @@
 // Marker -> grid: markers are binned by the node-grid cell that contains them
 // (the cell whose four corners are the nodes they weight) with a stable
 // two-level partition written here (see k_keys); each cell then sums, in
-// sorted order, the weighted values and weights its markers give to its four
+// a fixed order, the weighted values and weights its markers give to its four
 // corners, and each node adds the sums of its (up to) four cells in a fixed
 // order.  Every sum has one writer and a fixed order, so results are bitwise
 // reproducible.  Grid -> marker and RK4 are one thread per marker; all four
@@ -19,6 +19,7 @@
 
 #include "../../include/tephra.h"
 #include "devmem.h"
+#include "reduce.h"
 #include "solver_internal.h"
 
 struct tph_markers {
@@ -536,6 +537,18 @@ __device__ __forceinline__ void divided_factors(const NodeGrid& q, int nx, doubl
 // from 173 with a pass over partial sums in memory) and by the walk's operations.
 // ---------------------------------------------------------------------------
 constexpr int kNodeWaves = 4;
+// Runs (of 16 cells) beyond this many markers go cell by cell, 16 lanes a corner.  A lane a corner walks one marker
+// after the other at some 150 cycles each, and in a crowd, where a staged piece covers a cell or less, the other 60
+// wait: 4.2 M markers on 1024^2 cells, gathered in a tenth of the rows and columns (400 a cell), 4400 -> 380 us of
+// this kernel.  The line lies where both take the same: at 16 a cell (runs of 256) walking takes 196 us a call, cell
+// by cell 215; at 33 a cell 259 and 248.
+constexpr int kCrowd = 512;
+// sum over the sixteen lanes that share lane & 3, in all of them
+__device__ __forceinline__ double sixteen_sum(double v) {
+    v = tph::wave_add_rows(tph::wave_add_halves(v));
+    v += tph::row16_rotate<0x128>(v);
+    return v + tph::row16_rotate<0x124>(v);
+}
 __device__ __forceinline__ int stage_slot(int t) { return t + (t >> 4); }
 
 // every node of the range, where there are no markers
@@ -639,6 +652,43 @@ __global__ __launch_bounds__(kNodeWaves * 64) void k_nodes(NodeGrid q, int nx, i
         }
         if (u < ue) add(rx, ry, f);
     };
+    // A crowded run: one cell after the other, each by all lanes.  Sixteen lanes a corner take a cell's markers in
+    // turn (by their rank in the cell, whatever the pieces) and their sums are added in the tree of halving
+    // distances; lanes of cell c of the sixteen end with its sums.
+    auto walk_crowded = [&](int g, int P0, int P1, double yi) {
+        int c = 0, cs = P0, ce = __builtin_amdgcn_readlane(e, g * 16);
+        double own_num = 0.0, own_den = 0.0;
+        indices(P0 + kChunk, P1);
+#pragma unroll 1
+        for (int p = P0;; p += kChunk) {
+            gather();
+            indices(p + 2 * kChunk, P1);
+            const int pe = min(p + kChunk, P1);
+#pragma unroll 1
+            for (;;) {
+                const int u = max(cs, p);
+                for (int t = u + (((lane >> 2) - (u - cs)) & 15); t < min(ce, pe); t += 16) {
+                    const int q = stage_slot(t - p);
+                    add(sx[q], sy[q], sf[q]);
+                }
+                if (ce > pe || c == 15) break;
+                num = sixteen_sum(num);
+                den = sixteen_sum(den);
+                own_num = lane >> 2 == c ? num : own_num;
+                own_den = lane >> 2 == c ? den : own_den;
+                num = den = 0.0;
+                ++c;
+                cs = ce;
+                ce = __builtin_amdgcn_readlane(e, g * 16 + c);
+            }
+            if (p + kChunk >= P1) break;
+            to_lds(yi);
+        }
+        num = sixteen_sum(num);
+        den = sixteen_sum(den);
+        num = lane >> 2 == 15 ? num : own_num;
+        den = lane >> 2 == 15 ? den : own_den;
+    };
     auto run_of = [&](int g, int bb, int ee, int& P0, int& P1) {
         P0 = __builtin_amdgcn_readlane(bb, g * 16);
         P1 = __builtin_amdgcn_readlane(ee, g * 16 + 15);
@@ -680,13 +730,17 @@ __global__ __launch_bounds__(kNodeWaves * 64) void k_nodes(NodeGrid q, int nx, i
             indices(M0, M1);
             walk(cb, ce, P0);
         } else {
-            walk(cb, min(ce, P0 + kChunk), P0);
-            for (int p = P0 + kChunk; p < P1; p += kChunk) {
-                const int pe = min(p + kChunk, P1);
-                indices(p, pe);
-                gather();
-                to_lds(yi);
-                walk(max(cb, p), min(ce, pe), p);
+            if (P1 - P0 > kCrowd) {
+                walk_crowded(g, P0, P1, yi);
+            } else {
+                walk(cb, min(ce, P0 + kChunk), P0);
+                for (int p = P0 + kChunk; p < P1; p += kChunk) {
+                    const int pe = min(p + kChunk, P1);
+                    indices(p, pe);
+                    gather();
+                    to_lds(yi);
+                    walk(max(cb, p), min(ce, pe), p);
+                }
             }
             indices(N0, N1);
             gather();
