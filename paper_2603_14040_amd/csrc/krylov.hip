@@ -31,52 +31,64 @@ constexpr int kNV = 8;
 // two neighbouring entries (vectors are 256-byte aligned and of even length)
 typedef double D2 __attribute__((ext_vector_type(2)));
 
-// Partial sums of V_i . w for NV vectors per block (those from blockIdx.y * NV on);
-// index nv stands for w . w where norm_slot asks for it.  How many vectors share a block
-// does not change a sum (a block's threads, their strides and the tree over them
-// are the same), only the work in flight: long vectors take 8 per block, so w is
+// Partial sums of V_i . w for NV vectors per block, or one less: gridDim.y groups share the vectors evenly.  Index nv
+// stands for w . w where norm_slot asks for it (of the entry of w that every thread has anyway).  How many vectors
+// share a block does not change a sum (a block's threads, their strides and the tree over them
+// are the same), only the work in flight: long vectors take up to 8 per block, so w is
 // read once for them; short ones one each, so that every vector's loads and its
 // reduction run side by side (up to 8 vectors of 25 500 entries: 4.4 us, against
-// 11 us with all of them in each block and a barrier pair per vector).  Long
-// vectors are bound by the reads of V (16 vectors of 3.35 M entries: 72 us, 6 TB/s).
-template <int NV>
+// 11 us with all of them in each block and a barrier pair per vector).
+// Bound by the reads of V (16 vectors of 3.35 M entries: 72 us, 6 TB/s).  LONG (more than 8 entries a thread): one
+// load after the other, with all waves resident (1, 4, 8 and 16 vectors of 51 M entries: 128, 321, 575 and 1156 us; two
+// entries' loads together 152, 355, 661 and 1285; eight slots in every block, those without a vector reading w again,
+// 282, 382, 875 and 1514).  A kernel of its own: beside the other loop its scalar registers allow fewer waves than the
+// 2048 blocks have (8 vectors: 885 us).
+template <int NV, bool LONG>
 __global__ __launch_bounds__(256) void k_multidot(const double* __restrict__ V0, size_t vstride, int nv,
                                                  const double* __restrict__ w, size_t n,
                                                  double* __restrict__ partial, int nblk, int norm_slot, Again again) {
-    __shared__ double part[4 * NV];
+    __shared__ double part[4 * (NV + 1)];
     if (again.asked() && !again.needed()) return;
-    const int v0 = blockIdx.y * NV;
+    const int v0 = (int)(blockIdx.y * (unsigned)nv / gridDim.y), v1 = (int)((blockIdx.y + 1) * (unsigned)nv / gridDim.y);
     const double* V[NV];
 #pragma unroll
-    for (int v = 0; v < NV; ++v) V[v] = v0 + v < nv ? V0 + (v0 + v) * vstride : w;
-    double acc[NV];
+    for (int v = 0; v < NV; ++v) V[v] = v0 + v < v1 ? V0 + (v0 + v) * vstride : w;
+    double acc[NV + 1];
 #pragma unroll
-    for (int v = 0; v < NV; ++v) acc[v] = 0.0;
+    for (int v = 0; v <= NV; ++v) acc[v] = 0.0;
     const size_t step = (size_t)gridDim.x * 256;
     size_t t = blockIdx.x * (size_t)256 + threadIdx.x;
-    constexpr int U = NV >= 8 ? 2 : 8 / NV;          // entries in flight per thread
-    for (; t + (U - 1) * step < n; t += U * step) {
-        double x[U], y[U][NV];
+    if constexpr (!LONG) {
+        constexpr int U = NV >= 4 ? 2 : 8 / NV;      // entries in flight per thread
+        for (; t + (U - 1) * step < n; t += U * step) {
+            double x[U], y[U][NV];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            x[u] = w[t + u * step];
+            for (int u = 0; u < U; ++u) {
+                x[u] = w[t + u * step];
 #pragma unroll
-            for (int v = 0; v < NV; ++v) y[u][v] = V[v][t + u * step];
+                for (int v = 0; v < NV; ++v) y[u][v] = V[v][t + u * step];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+#pragma unroll
+                for (int v = 0; v < NV; ++v) acc[v] += y[u][v] * x[u];
+                acc[NV] += x[u] * x[u];
+            }
         }
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int v = 0; v < NV; ++v) acc[v] += y[u][v] * x[u];
     }
     for (; t < n; t += step) {
         const double x = w[t];
 #pragma unroll
-        for (int v = 0; v < NV; ++v) acc[v] += V[v][t] * x;
+        for (int v = 0; v < NV; ++v) {
+            acc[v] += V[v][t] * x;
+            if (LONG) __builtin_amdgcn_sched_barrier(0);
+        }
+        acc[NV] += x * x;
     }
     const double s = block_sums(acc, part);
-    const int v = v0 + threadIdx.x;
-    if (threadIdx.x < NV && (v < nv || (v == nv && norm_slot >= 0)))
-        partial[(size_t)(v < nv ? v : norm_slot) * nblk + blockIdx.x] = s;
+    const int v = threadIdx.x;
+    if (v < v1 - v0) partial[(size_t)(v0 + v) * nblk + blockIdx.x] = s;
+    if (v == NV && blockIdx.y == 0 && norm_slot >= 0) partial[(size_t)norm_slot * nblk + blockIdx.x] = s;
 }
 
 // Sums of U rows of at most kSumBlocks block sums (r, r + step, .. below k; valid in lane 0): a wave a row, the
@@ -105,7 +117,10 @@ __device__ __forceinline__ void wave_row_sums(const double* __restrict__ partial
 
 // w -= sum_i h[i] V_i for any number of vectors, with the block sums of the new
 // w . w, in one pass over w (8 vectors' loads in flight at a time; a launch per 8
-// vectors re-read w and paid 5 us each on short vectors)
+// vectors re-read w and paid 5 us each on short vectors).  U entries a thread at once: 4 while its blocks
+// leave the chip idle, 2 beyond 256 blocks, 1 where its strides over a long vector lie far apart (sums over 24
+// steps: 290 k entries 452 us with 4, 481 with 2; 630 k 697, 673; 12.9 M entries and one vector 57 with 2, 47 with 1).
+template <int U>
 __global__ __launch_bounds__(256) void k_axpy_norm(double* __restrict__ w, const double* __restrict__ V0,
                                                   size_t vstride, int nv, const double* __restrict__ h, size_t n,
                                                   double* __restrict__ partial, Again again) {
@@ -113,7 +128,6 @@ __global__ __launch_bounds__(256) void k_axpy_norm(double* __restrict__ w, const
     if (again.asked() && !again.needed()) return;
     double acc[1] = {0.0};
     const size_t step = (size_t)gridDim.x * 256;
-    constexpr int U = 4;
     for (size_t t0 = blockIdx.x * (size_t)256 + threadIdx.x; t0 < n; t0 += U * step) {
         double x[U];
         bool in[U];
@@ -325,30 +339,26 @@ __global__ __launch_bounds__(256) void k_update_x(const UpdateArgs a) {
 //   r -= alpha w^
 // and, when z is given, z' = (z - sum_j hz_j Z_j) / nu, x += alpha z'.
 // The coefficients travel in the kernel arguments (uniform scalar loads).
+// One entry a thread: with 2048 blocks that stride over the vectors, long ones took 7 to 10 % more (51 M entries,
+// 24 steps: 31.2 ms, now 28.1; two entries a thread 29.1, and 33.1 with 2048 blocks; 3.3 M entries 1.75, now 1.66).
 __global__ __launch_bounds__(256) void k_gcr_step(const GcrStepArgs a) {
-    auto project = [&](D2 x, const double* h, const double* V0, size_t t) {
-        for (int v0 = 0; v0 < a.i; v0 += kNV) {
-            D2 y[kNV];
-#pragma unroll
-            for (int v = 0; v < kNV; ++v)
-                y[v] = v0 + v < a.i ? *(const D2*)(V0 + (v0 + v) * a.stride + t) : D2{0.0, 0.0};
-#pragma unroll
-            for (int v = 0; v < kNV; ++v) x -= (v0 + v < a.i ? h[v0 + v] : 0.0) * y[v];
-        }
-        return x;
-    };
-    for (size_t t = 2 * (blockIdx.x * (size_t)256 + threadIdx.x); t < a.n; t += (size_t)512 * gridDim.x) {
-        D2 wv = *(const D2*)(a.w + t);
-        const D2 r = *(const D2*)(a.r + t);
-        if (a.orth_w) wv = project(wv, a.hw, a.W0, t);
-        wv *= a.inv_nu;
-        *(D2*)(a.w + t) = wv;
-        *(D2*)(a.r + t) = r - a.alpha * wv;
-        if (a.z) {
-            const D2 zv = project(*(const D2*)(a.z + t), a.hz, a.Z0, t) * a.inv_nu;
-            *(D2*)(a.z + t) = zv;
-            *(D2*)(a.x + t) = *(const D2*)(a.x + t) + a.alpha * zv;
-        }
+    const size_t t = blockIdx.x * (size_t)256 + threadIdx.x;
+    if (t >= a.n) return;
+    double wv = a.w[t];
+    if (a.orth_w) {
+#pragma unroll 4
+        for (int j = 0; j < a.i; ++j) wv -= a.hw[j] * a.W0[j * a.stride + t];
+    }
+    wv *= a.inv_nu;
+    a.w[t] = wv;
+    a.r[t] -= a.alpha * wv;
+    if (a.z) {
+        double zv = a.z[t];
+#pragma unroll 4
+        for (int j = 0; j < a.i; ++j) zv -= a.hz[j] * a.Z0[j * a.stride + t];
+        zv *= a.inv_nu;
+        a.z[t] = zv;
+        a.x[t] += a.alpha * zv;
     }
 }
 
@@ -431,21 +441,44 @@ __global__ __launch_bounds__(256) void k_p_shift(Geom g, double* __restrict__ p,
 
 hipError_t launch_multidot(const double* V0, size_t vstride, int nv, const double* w, size_t n, double* partial,
                            int nblk, hipStream_t st, int norm_slot, Again again) {
-    const int rows = nv + (norm_slot >= 0 ? 1 : 0);
-    // vectors per block: 8 once the blocks of one group fill the chip by
+    // vectors per block: up to 8 once the blocks of one group fill the chip by
     // themselves (two per CU), fewer while they do not; nblk is n / 2048
     const int per = nblk >= 512 ? 8 : nblk >= 128 ? 4 : 1;
-#define TPH_DOT(NV)                                                                                                    hipLaunchKernelGGL((k_multidot<NV>), dim3(nblk, (rows + NV - 1) / NV), dim3(256), 0, st, V0, vstride, nv, w, n,                        partial, nblk, norm_slot, again)
-    if (per == 8) TPH_DOT(8);
-    else if (per == 4) TPH_DOT(4);
-    else TPH_DOT(1);
+    const int groups = (nv + per - 1) / per;
+    if (groups < 1) return hipErrorInvalidValue;
+    const dim3 grid(nblk, groups);
+    const bool lng = n > (size_t)2048 * nblk;        // the block count is at its most
+#define TPH_DOT(NV)                                                                                                    \
+    case NV:                                                                                                           \
+        if (lng)                                                                                                       \
+            hipLaunchKernelGGL((k_multidot<NV, true>), grid, dim3(256), 0, st, V0, vstride, nv, w, n, partial, nblk,   \
+                               norm_slot, again);                                                                      \
+        else                                                                                                           \
+            hipLaunchKernelGGL((k_multidot<NV, false>), grid, dim3(256), 0, st, V0, vstride, nv, w, n, partial, nblk,  \
+                               norm_slot, again);                                                                      \
+        break;
+    switch ((nv + groups - 1) / groups) {            // the largest group's
+        TPH_DOT(1)
+        TPH_DOT(2)
+        TPH_DOT(3)
+        TPH_DOT(4)
+        TPH_DOT(5)
+        TPH_DOT(6)
+        TPH_DOT(7)
+        TPH_DOT(8)
+    }
 #undef TPH_DOT
     return hipGetLastError();
 }
 
 hipError_t launch_axpy_norm(double* w, const double* V0, size_t vstride, int nv, const double* h, size_t n,
                             double* partial, int nblk, hipStream_t st, Again again) {
-    hipLaunchKernelGGL(k_axpy_norm, dim3(nblk), dim3(256), 0, st, w, V0, vstride, nv, h, n, partial, again);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(nblk), dim3(256), 0, st, w, V0, vstride, nv, h, n, partial, again);
+    };
+    if (n > (size_t)2048 * nblk) launch(k_axpy_norm<1>);
+    else if (nblk > 256) launch(k_axpy_norm<2>);
+    else launch(k_axpy_norm<4>);
     return hipGetLastError();
 }
 
@@ -489,9 +522,8 @@ hipError_t launch_update_x(double* x, const double* Z0, size_t zstride, int k, c
 }
 
 hipError_t launch_gcr_step(const GcrStepArgs& a, hipStream_t st) {
-    if (a.i < 0 || a.i > kMaxRestart || (a.n & 1) || (a.stride & 1)) return hipErrorInvalidValue;
-    const size_t b = (a.n + 511) / 512;
-    hipLaunchKernelGGL(k_gcr_step, dim3((unsigned)(b < 1 ? 1 : b > 2048 ? 2048 : b)), dim3(256), 0, st, a);
+    if (a.i < 0 || a.i > kMaxRestart || a.n < 1) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_gcr_step, dim3((unsigned)((a.n + 255) / 256)), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 
