@@ -521,16 +521,15 @@ class Markers:
 
     def to_grid(self, kind: str, xm, ym, fields, fill: float = 0.0):
         """Normalised bilinear averages of each marker field on the `kind` nodes (one binning)."""
-        n = xm.numel()
+        n, fields = xm.numel(), list(fields)
+        # zeroed before the marker stream is made to wait: behind it, the zeros would race the averages
+        outs = [torch.zeros(self.shape, dtype=torch.float64, device=self.device) for _ in fields]
         self._sync_in()
         _lib.check("tph_markers_bin", self._lib.tph_markers_bin(self._h, _lib.NODE_KINDS[kind], n,
                                                                 _mptr(xm, n, "xm"), _mptr(ym, n, "ym")))
-        outs = []
-        for k, f in enumerate(fields):
-            g = torch.zeros(self.shape, dtype=torch.float64, device=self.device)
+        for k, (f, g) in enumerate(zip(fields, outs)):
             _lib.check("tph_markers_to_grid", self._lib.tph_markers_to_grid(self._h, _mptr(f, n, f"fields[{k}]"),
                                                                             float(fill), _ptr(g, self.shape, "grid")))
-            outs.append(g)
         self._sync_out()
         return outs
 
