@@ -358,6 +358,11 @@ tph_status tph_level_shape(tph_solver* s, int32_t level, int32_t* nx, int32_t* n
  * level reports kind 0.  Either output may be NULL. */
 tph_status tph_level_plan(tph_solver* s, int32_t level, int32_t* kind, int32_t* shape);
 
+/* Gram-Schmidt steps of this solver's FGMRES and GCR solves so far whose new
+ * vector was projected a second time (its norm fell below 1 / sqrt(2) of what
+ * it was before the first projection). */
+tph_status tph_second_projections(tph_solver* s, int64_t* count);
+
 /* Adjoint solve A^T lam = g (A is symmetric, so this is the forward solver
  * with right-hand side g = (gvx, gvy, gp)); lam is written zero-mean in
  * pressure.  Any of gvx, gvy, gp may be NULL (zero). */

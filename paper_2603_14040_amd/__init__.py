@@ -213,6 +213,13 @@ class Solver:
         _lib.check("tph_level_plan", self._lib.tph_level_plan(self._h, level, ctypes.byref(k), ctypes.byref(s)))
         return self.LEVEL_KINDS[k.value], s.value
 
+    @property
+    def second_projections(self) -> int:
+        """Krylov steps so far that projected their new vector twice (tph_second_projections)."""
+        n = ctypes.c_int64()
+        _lib.check("tph_second_projections", self._lib.tph_second_projections(self._h, ctypes.byref(n)))
+        return n.value
+
     def set_coefficients(self, eta_b, eta_p, rho_b, gx: float = 0.0, gy: float = -1.0,
                          fx_extra=None, fy_extra=None):
         self.generation += 1

@@ -8,7 +8,7 @@ from __future__ import annotations
 import ctypes
 import os
 import re
-from ctypes import POINTER, c_char_p, c_double, c_int32, c_size_t, c_uint64, c_void_p
+from ctypes import POINTER, c_char_p, c_double, c_int32, c_int64, c_size_t, c_uint64, c_void_p
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libtephra.so")
@@ -98,6 +98,7 @@ def load(path: str = LIB_PATH):
         "tph_level_viscosity": (c_int32, [P, c_int32, P, P]),
         "tph_level_shape": (c_int32, [P, c_int32, POINTER(c_int32), POINTER(c_int32)]),
         "tph_level_plan": (c_int32, [P, c_int32, POINTER(c_int32), POINTER(c_int32)]),
+        "tph_second_projections": (c_int32, [P, POINTER(c_int64)]),
         "tph_solve_adjoint": (c_int32, [P, P, P, P, P, P, P, POINTER(Info)]),
         "tph_coeff_gradient": (c_int32, [P, P, P, P, P, P, P, P, P, P]),
         "tph_time_kernel": (c_int32, [P, c_int32, c_int32, POINTER(c_double), POINTER(c_double)]),

@@ -120,7 +120,7 @@ struct tph_solver {
     bool ready = false;
     double bnorm = 0;
     double t_setup_ms = 0;
-    long long reorth_count = 0;  // second Gram-Schmidt passes taken (diagnostic)
+    int64_t reorth_count = 0;    // second Gram-Schmidt passes taken (tph_second_projections)
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     // optional event timing of one kernel class inside solves (the finest-level
     // smoother or the Uzawa link, tph_kernel_timing_target)
@@ -2189,6 +2189,13 @@ tph_status tph_level_plan(tph_solver* s, int32_t level, int32_t* kind, int32_t* 
     }
     if (kind) *kind = k;
     if (shape) *shape = (int32_t)((s->shape_mask >> level) & 1u);
+    return TPH_OK;
+}
+
+tph_status tph_second_projections(tph_solver* s, int64_t* count) {
+    g_last_error.clear();
+    if (!s || !count) { set_error("solver and count are required"); return TPH_ERR_INVALID; }
+    *count = s->reorth_count;
     return TPH_OK;
 }
 
