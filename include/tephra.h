@@ -500,7 +500,7 @@ enum { TPH_NODES_BASIC = 0, TPH_NODES_CELL = 1, TPH_NODES_VX = 2, TPH_NODES_VY =
 typedef struct tph_markers tph_markers;
 
 /* Workspace for an nx x ny grid of size lx x ly and up to `capacity`
- * markers (sort buffers, per-cell ranges and partial sums).  Errors:
+ * markers (sort buffers, counts and per-cell ranges).  Errors:
  * TPH_ERR_INVALID for bad sizes, TPH_ERR_OOM. */
 tph_status tph_markers_create(int32_t nx, int32_t ny, double lx, double ly, int32_t capacity, void* hip_stream,
                               tph_markers** out);

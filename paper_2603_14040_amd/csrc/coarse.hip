@@ -2,8 +2,9 @@
 // correction equation is solved directly).  The dense matrix M = -L of the
 // coarsest level (symmetric positive definite) is assembled on the device
 // from the rediscretised stencil, inverted once per coefficient set by an
-// in-place Gauss-Jordan sweep in a single workgroup, and applied as a dense
-// matrix-vector product (one wavefront per row).  Unknown order: vx(i, j)
+// in-place Gauss-Jordan elimination (a single problem's in panels of 32 steps
+// over the device, a batch's small ones by one workgroup each), and applied as a
+// dense matrix-vector product (one wavefront per row).  Unknown order: vx(i, j)
 // row-major (i in [1, ny], j in [1, nx-1]), then vy(i, j) (i in [1, ny-1],
 // j in [1, nx]).
 #include "kernels.h"

@@ -56,7 +56,7 @@ size_t coarse_cycle_lds_bytes(const Geom* g, int nl, int nc) {
 }
 
 // as few threads as own the top level's cell pairs one each (fewer waves meet
-// at every barrier); two pairs per thread beyond 1024
+// at every barrier); two pairs per thread beyond 512, four beyond 1024
 TailShape coarse_cycle_shape(int nx, int ny) {
     const int pairs = (nx / 2) * ny;
     if (pairs <= 256) return {256, 1};

@@ -35,31 +35,6 @@ __device__ __forceinline__ double fma_(double a, double b, double c) { return __
 enum { kModePlain = kTilePlain, kModeZero = kTileZero, kModeProlong = kTileProlong };
 enum { kSmJacobi = 0, kSmGS = 1 };
 
-// Bilinear prolongation of the coarse vx / vy correction to fine node (i, j)
-// (same weights as k_prolong_add; coarse ghosts hold mirrored values).  A node on
-// a coarse column (row) reads it twice with half the weight, which is exact:
-// neighbouring lanes then take one path (2048^2 sweep with prolongation 43 -> 40
-// us from this alone).
-template <typename T>
-__device__ __forceinline__ T prolong_vx(const T* __restrict__ ec, int Pc, int i, int j) {
-    const int I0 = (i + 1) >> 1;
-    const int I1 = (i & 1) ? I0 - 1 : I0 + 1;
-    const int J = j >> 1, e = j & 1;
-    const T* a = ec + (I0 * Pc + J);
-    const T* b = ec + (I1 * Pc + J);
-    return (T)0.375 * (a[0] + a[e]) + (T)0.125 * (b[0] + b[e]);
-}
-
-template <typename T>
-__device__ __forceinline__ T prolong_vy(const T* __restrict__ ec, int Pc, int i, int j) {
-    const int J0 = (j + 1) >> 1;
-    const int J1 = (j & 1) ? J0 - 1 : J0 + 1;
-    const int I = i >> 1, e = (i & 1) ? Pc : 0;
-    const T* a = ec + (I * Pc + J0);
-    const T* b = ec + (I * Pc + J1);
-    return (T)0.375 * (a[0] + a[e]) + (T)0.125 * (b[0] + b[e]);
-}
-
 __device__ __forceinline__ bool is_vx(const Geom& g, int i, int j) { return i >= 1 && i <= g.ny && j >= 1 && j < g.nx; }
 __device__ __forceinline__ bool is_vy(const Geom& g, int i, int j) { return i >= 1 && i < g.ny && j >= 1 && j <= g.nx; }
 
@@ -110,11 +85,11 @@ constexpr int prolong_rows() { return RH / 2 + 4; }
 // slower again), with bitwise the same results, since nodes of one stage
 // are independent of each other.
 constexpr int kTileThreads = 512;
-// Waves per SIMD the one-sweep tile kernels are compiled for: 8, i.e. at most
-// 64 registers, so that four workgroups share a CU and the 1024 tiles of a
-// 1024^2 level run in one round (the sweep with prolongation took 66 by itself,
-// three per CU and a second, nearly empty round: 16.6 us, now 16.3 from this
-// alone).
+// Waves per SIMD the one-sweep tile kernels ask for: 8, so that four workgroups
+// share a CU and the 1024 tiles of a 1024^2 level run in one round.  The FP32 sweep
+// with prolongation gets there with 61 registers (66 by itself, three workgroups per
+// CU and a second, nearly empty round: 16.6 us, now 16.3 from this alone).  The
+// FP64 one takes 77: its 44.5 KB of LDS allow three workgroups in any case.
 constexpr int kTileWaves = 8;
 
 template <int N>
@@ -232,7 +207,7 @@ __device__ __forceinline__ void tile_load(const Geom& g, const Geom& gc, int gi0
         } else {
             V2 ux = vx[it], uy = vy[it];
             if (MODE == kModeProlong) {
-                // bilinear, the weights and order of prolong_vx / prolong_vy; coarse
+                // bilinear, the weights of k_prolong_add (coarse ghosts hold mirrored values); coarse
                 // rows and columns relative to the LDS window.  Columns gj = 2M + 1 (between
                 // coarse lines M, M + 1 for vx) and gj + 1 (on line M + 1).
                 const int gi = gi0 + a, gj = gj0 + 2 * m;

@@ -328,7 +328,7 @@ __global__ __launch_bounds__(1024, 8) void k_digit_scatter(const uint32_t* __res
     for (int k = 0; k < R; ++k) {
         const uint32_t d = (key[k] >> shift) & mask;
         at[k] = wave_rank<true>(d, m0 + k * 64 < left, 0, wcnt + w * ndig);
-        __builtin_amdgcn_sched_barrier(0);       // one round at a time: their temporaries together do not fit
+        __builtin_amdgcn_sched_barrier(0);       // one round at a time: of their temporaries together more would spill
     }
     __syncthreads();
     for (int d = threadIdx.x; d < ndig; d += 1024) {
@@ -344,7 +344,7 @@ __global__ __launch_bounds__(1024, 8) void k_digit_scatter(const uint32_t* __res
 #pragma unroll
     for (int k = 0; k < R; ++k) {
         const int m = m0 + k * 64;
-        asm("" : "+v"(key[k]));                  // the digit anew: 16 digits and addresses kept would spill
+        asm("" : "+v"(key[k]));                  // the digit anew: 16 digits and addresses kept would spill (9 registers do)
         if (m < left) {
             const uint32_t d = (key[k] >> shift) & mask;
             const uint32_t pos = (uint32_t)base[d] + wcnt[w * ndig + d] + at[k];
@@ -369,7 +369,7 @@ __device__ __forceinline__ int lower_bound(const uint32_t* __restrict__ keys, in
 // up to 10240 markers is ranked once, in registers; a longer one is counted first and goes in pieces.
 // K as in k_digit_scatter: the bucket's run comes from the digit totals (uint16_t), or from a search in
 // the sorted keys (uint32_t).  1024^2 cells, 16 markers each: 80 us with six waves a SIMD (eight: 91 us,
-// with 20 registers spilled; five: 101 us).
+// with 20 registers spilled; five: 101 us).  At six the four-wave kernel still spills 12, the eight-wave one 4.
 template <int NW, typename K>
 __global__ __launch_bounds__(NW * 64, 6) void k_cell_sort(const K* __restrict__ kin, const int32_t* __restrict__ vin, int n,
                                                     int shift, int ncell, const int32_t* __restrict__ total,
@@ -899,6 +899,8 @@ constexpr int kMaxMarkers = 1 << 28;
 
 // One cell row a wave while a small grid leaves the chip idle, two on larger ones: an eighth of the rows is then
 // done twice (four rows: 172 us instead of 157 at 1024^2, with too few workgroups for an even last wave).
+// A binning and six fields of 9 markers a cell, one row a wave and two: 300^2 cells 138 and 156 us, 500^2 223 and
+// 227, 547^2 240 and 226, 1024^2 577 and 538; with 4 a cell both meet near 700^2, with 16 near 400^2.
 constexpr long long kRowCells = 300000;
 
 // How the bits of a key are divided: the lowest `shift` within a bucket, the rest in one pass or two.

@@ -23,11 +23,13 @@
 //     owned values wait in registers, and its viscosities and right-hand side
 //     never enter LDS.
 // Every node goes through the operations of the level-by-level kernels in their
-// order (lx_row, relax, restrict_cell, prolong_vx and their mirrors, the dense
-// product by 16 lanes a row), so the cycle gives the same bits.
+// order (lx_row, relax, restrict_cell, the bilinear prolongation and their mirrors, the
+// dense product by 16 lanes a row), so the cycle gives the same bits.
 // Measured, one launch, 32 x 32 top, three levels: FP32 17 us with 1 + 1 sweeps
 // (27 us with a thread per node, its stencil read from LDS in every phase), 18 us
 // with 2 + 2 (36); FP64 24 us with 2 + 2 (47).
+// Registers: 222 to 282, one or two waves a SIMD; the shapes of two and four pairs a thread in
+// FP64 and FP32 spill 18 and 8 of them (22 and 2 in the batch).
 // KP pairs per thread cover the top level; the levels below it have a quarter
 // of its cells, so one pair per thread covers them.
 #pragma once
