@@ -89,11 +89,17 @@ __device__ __forceinline__ int item_index() {
 }
 
 // ------------------------------------------------------------------ V-cycle
+// One-sweep tile over the tiles of one depth.  At most 80 scalar registers:
+// above that a SIMD holds 7 of these waves instead of 8, which is 3
+// workgroups per CU instead of 4.  Without the bound the FP32 Gauss-Seidel
+// instances take 82 (from the iterate) and 93 (with the prolongation); with
+// it 4 and 15 scalars wait in lanes of a vector register, and the launches of
+// a batch of 256 sinkers (2 + 2 sweeps, 64^2 to 512^2) take 42.9 us instead
+// of 47.6 and 55.2 instead of 62.4.
 template <typename T, int SM, int MODE>
-__global__ __launch_bounds__(kTileThreads) void kb_smooth_tile(const BLevel<T>* __restrict__ lev,
-                                                     const BProb* __restrict__ prob, const int2* __restrict__ items,
-                                                     const int* __restrict__ active, int depth, int src, int dst,
-                                                     int ccur_post, T omega) {
+__global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_num_sgpr(80))) void kb_smooth_tile(
+    const BLevel<T>* __restrict__ lev, const BProb* __restrict__ prob, const int2* __restrict__ items,
+    const int* __restrict__ active, int depth, int src, int dst, int ccur_post, T omega) {
     const int2 it = items[item_index()];
     const int p = it.x;
     if (!active[p]) return;
