@@ -851,7 +851,9 @@ __global__ __launch_bounds__(256) void k_from_grid(NodeGrid q, int n, const doub
 // KEEP, for many markers: bound by the gathers of the velocity (16 loads a marker).  A stage moves a marker by a
 // fraction of a cell in a usual step: most lanes are still in the cell of the stage before and keep its nodes.
 // Otherwise, for few: bound by the latency of four gathers in a row, with no branch between them.  500, 65 000,
-// 130 000, 270 000 and 2.9 M markers: 3.1, 4.1, 4.7, 7.1 and 37.0 us with, 2.6, 3.7, 4.6, 7.4 and 43.1 without.
+// 130 000, 270 000 and 2.9 M markers: 3.1, 4.1, 4.7, 7.1 and 37.0 us with, 2.6, 3.7, 4.6, 7.4 and 43.1 without,
+// sorted by cell.  In random order keeping pays earlier: whole calls of 32 000, 65 000, 100 000 and 200 000 markers
+// take 19.4, 19.5, 20.0 and 23.3 us with, 19.4, 20.2, 23.3 and 31.0 without; the line lies between.
 template <bool KEEP>
 __global__ __launch_bounds__(256) void k_rk4(NodeGrid qx, NodeGrid qy, double lx, double ly, int n,
                                              double* __restrict__ xm, double* __restrict__ ym,
@@ -890,7 +892,7 @@ __global__ __launch_bounds__(256) void k_rk4(NodeGrid qx, NodeGrid qy, double lx
     ym[m] = clampy(y + dt / 6.0 * (k1y + 2.0 * k2y + 2.0 * k3y + k4y));
 }
 
-constexpr int kFewMarkers = 200000;
+constexpr int kFewMarkers = 60000;
 
 inline unsigned blocks(long long n) { return (unsigned)((n + 255) / 256); }
 
